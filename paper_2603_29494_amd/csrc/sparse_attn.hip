@@ -26,6 +26,7 @@
 // ds_read_b64_tr_b16, per group of 16 lanes: lane 4p + c receives as element q
 // the c-th 16-bit value at the address supplied by lane 4q + p.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.h"
 #include "launch.h"
@@ -84,6 +85,13 @@ __device__ __forceinline__ void ids_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t
 #endif
 }
 
+// Lane u of each row of 16 lanes, to all lanes of that row (a DPP operand of
+// the instruction that uses it).
+template <int U>
+__device__ __forceinline__ int row_bcast(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, 0x150 + U, 0xf, 0xf, true);
+}
+
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -94,9 +102,11 @@ __device__ __forceinline__ void wait_vmcnt() {
 // SAME_STRIDE: K and V rows have the same stride, so a gathered row's K and V
 // offsets coincide.  ROWS: query rows per workgroup (64: 4 waves, or 128: 8
 // waves, for blocks of a multiple of 128 rows, so that one gather of a tile
-// serves all 128 rows of the block).
+// serves all 128 rows of the block).  Held to two waves per SIMD (256
+// registers): with one, nothing hides a wave's waits (dense keys, 64-row
+// workgroups, 299 registers: 1.66 ms where two waves take 1.17).
 template <int D, bool SAME_STRIDE, int ROWS>
-__global__ __launch_bounds__(4 * ROWS) void k_sparse_attn(
+__global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) void k_sparse_attn(
     const uint16_t* __restrict__ q, int64_t q_sB, int64_t q_sH, int64_t q_sN,
     const uint16_t* __restrict__ k, int64_t k_sB, int64_t k_sH, int64_t k_sN,
     const uint16_t* __restrict__ v, int64_t v_sB, int64_t v_sH, int64_t v_sN,
@@ -193,6 +203,8 @@ __global__ __launch_bounds__(4 * ROWS) void k_sparse_attn(
   const int xcd = blockIdx.x & 7;  // the hardware deals workgroup x to XCD x % 8
   const bool herd = !causal;
   __shared__ int s_rot;
+  __shared__ int s_redo;  // some wave's O or l is not finite after the first walk
+  if (threadIdx.x == 0) s_redo = 0;
   if (threadIdx.x == 0 && !herd) s_rot = 0;
   if (threadIdx.x == 0 && herd) {
     const unsigned int progress =
@@ -267,26 +279,48 @@ __global__ __launch_bounds__(4 * ROWS) void k_sparse_attn(
     const int L = (wave * U + u) * 64 + lane;
     return (L % CH) ^ swz<D>(L / CH);
   };
-  int nid[U];  // key ids of the next tile to issue (raw; clamped when used)
+  // Key ids of the next tile to gather (raw; clamped when used).  With
+  // 16-chunk rows (D = 128) a row's 16 lanes are one DPP row, so one load
+  // brings all U ids of the lane (lane u of a DPP row holds the id of
+  // instruction u) and the gather's offset reads its own with a DPP
+  // broadcast: U - 1 fewer vector-memory instructions per wave and tile.
+  constexpr bool kRowIds = CH == 16 && U <= 4;
+  constexpr int kIdRegs = kRowIds ? 1 : U;
+  int nid[kIdRegs];
 
   auto load_ids = [&](int t) __attribute__((always_inline)) {
     const __amdgpu_buffer_rsrc_t rs = tile_rsrc(t);
+    if constexpr (kRowIds) {
+      const int row = (wave * U + (lane & (U - 1))) * 4 + (lane >> 4);
+      nid[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, row * 4, 0, 0);
+    } else {
 #pragma unroll
-    for (int u = 0; u < U; ++u) nid[u] = __builtin_amdgcn_raw_buffer_load_b32(rs, grow(u) * 4, 0, 0);
-  };
-  auto issue_tile = [&](int t, int st) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      // Valid ids are below N < 2^24 and row strides below 2^24 bytes, as
-      // __umul24 needs; an invalid id reads some row of this head or zeros,
-      // never outside it (buffer range check).
-      const uint32_t r = static_cast<uint32_t>(nid[u]);
-      uint16_t* kd = kbuf(st) + (wave * U + u) * 64 * 8;
-      uint16_t* vd = vbuf(st) + (wave * U + u) * 64 * 8;
-      const uint32_t ko = __umul24(r, k_rowb) + 16u * gcol(u);
-      gather16_to_lds(krs, ko, kd);
-      gather16_to_lds(vrs, SAME_STRIDE ? ko : __umul24(r, v_rowb) + 16u * gcol(u), vd);
+      for (int u = 0; u < U; ++u) nid[u] = __builtin_amdgcn_raw_buffer_load_b32(rs, grow(u) * 4, 0, 0);
     }
+  };
+  auto id_of = [&](int u) __attribute__((always_inline)) {
+    if constexpr (kRowIds) {
+      return u == 0 ? row_bcast<0>(nid[0]) : u == 1 ? row_bcast<1>(nid[0])
+             : u == 2 ? row_bcast<2>(nid[0]) : row_bcast<3>(nid[0]);
+    } else {
+      return nid[u];
+    }
+  };
+  // Gather n of the 2 U of a tile: the K rows of instruction n / 2, then its V
+  // rows.  Valid ids are below N < 2^24 and row strides below 2^24 bytes, as
+  // __umul24 needs; an invalid id reads some row of this head or zeros, never
+  // outside it (buffer range check).
+  auto gather = [&](int n, int st) __attribute__((always_inline)) {
+    const int u = n / 2;
+    const uint32_t r = static_cast<uint32_t>(id_of(u));
+    if (n % 2 == 0) {
+      gather16_to_lds(krs, __umul24(r, k_rowb) + 16u * gcol(u), kbuf(st) + (wave * U + u) * 64 * 8);
+    } else {
+      gather16_to_lds(vrs, __umul24(r, SAME_STRIDE ? k_rowb : v_rowb) + 16u * gcol(u),
+                      vbuf(st) + (wave * U + u) * 64 * 8);
+    }
+  };
+  auto stage_ids = [&](int t, int st) __attribute__((always_inline)) {
     if (wave == 0)  // the tile's key ids (past count: 0, and masked)
       ids_to_lds(tile_rsrc(t), static_cast<uint32_t>(lane) * 4u, ibuf(st));
   };
@@ -294,48 +328,84 @@ __global__ __launch_bounds__(4 * ROWS) void k_sparse_attn(
   f32x16 oacc[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) oacc[db] = f32x16{};
-  float m_run = kNegInf;  // reference max (log2 units) this lane's row is scaled against
-  float l_run = 0.0f;     // this lane's partial normaliser
+  // Reference (log2 units) this lane's row is scaled against; kUnseen until the
+  // row has met a visible key.
+  constexpr float kUnseen = -3.4028234663852886e38f;
+  float m_run = kUnseen;
+  float l_run = 0.0f;   // this lane's partial normaliser
+  int settled = 0;      // every row of the wave has a reference
+  int careful = 0;      // second walk: references are fixed before the weights
 
-  if (ntiles > 0) {
-    load_ids(0);
-    issue_tile(0, 0);
-    load_ids(1);
-  }
-
-  // Per-lane constants of the LDS reads.
-  const int krow = 32 * kw + ln;
-  const int ksw = swz<D>(krow);
+  // Per-lane byte offsets of the LDS reads inside a stage, opaque to the
+  // compiler so that each stage's address is a constant offset from them (one
+  // register per offset for all stages, not one per stage).
   const int j16 = lane & 15;
   const int tq = j16 >> 2, tp = j16 & 3;
   const int vhalf = (lane >> 4) & 1;
+  uint32_t koff[DS], voff[DB][2];
+#pragma unroll
+  for (int s2 = 0; s2 < DS; ++s2) {
+    const int krow = 32 * kw + ln;
+    koff[s2] = krow * RB + 16 * ((2 * s2 + g) ^ swz<D>(krow));
+    asm volatile("" : "+v"(koff[s2]));
+  }
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int hi = 0; hi < 2; ++hi) {
+      const int d = 32 * db + 16 * vhalf + 4 * tp;   // first of the 4 head-dim values addressed
+      const int k0 = 32 * kw + 4 * g + tq + 8 * hi;  // key row this lane addresses (K-step 0)
+      voff[db][hi] = k0 * RB + 16 * ((d >> 3) ^ swz<D>(k0)) + 8 * ((d >> 2) & 1);
+      asm volatile("" : "+v"(voff[db][hi]));
+    }
 
-  auto step = [&](const int t, const int st) __attribute__((always_inline)) {
+  // One tile.  MORE: tile t + 1 exists and is gathered meanwhile.
+  auto step = [&](const int t, const int st, auto more_tag) __attribute__((always_inline)) {
+    constexpr bool MORE = decltype(more_tag)::value;
     // Tile t has landed, and the ids of tile t+1 (issued right after it) too;
     // the barrier (no fence: all LDS traffic here is waited for explicitly)
     // also guarantees every wave is done reading the other stage.
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
-    if (herd && wave == 0 && lane == 0 && (t % kHerdBatch) == kHerdBatch - 1)
+    if (herd && !careful && wave == 0 && lane == 0 && (t % kHerdBatch) == kHerdBatch - 1)
       __hip_atomic_fetch_add(&g_herd[xcd], herd_units(t + 1) - herd_units(t + 1 - kHerdBatch),
                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (t + 1 < ntiles) issue_tile(t + 1, st ^ 1);
-    load_ids(t + 2);  // past the list these read 0
+    if (MORE) stage_ids(t + 1, st ^ 1);
 
-    // S^T = K_tile Q^T for this wave's 32 keys x 32 rows.
+    // S^T = K_tile Q^T for this wave's 32 keys x 32 rows, and between its MFMAs
+    // the gathers of tile t + 1.  A gather holds the CU's address path 16
+    // cycles (1 KB at 64 B per cycle) and a wave that issues while the path is
+    // full waits; the workgroup's gathers issued in one burst before the MFMAs
+    // cost the step those ~512 cycles (2155 cycles per tile with two workgroups
+    // on a CU, 1521 with the tiles resident), one per MFMA runs them beside the
+    // matrix pipe (1842; 75k DiT layer 5.29 -> 4.87 ms per 10 heads, 119k DiT
+    // 14.5 -> 13.7 per 6).  Issued any later (softmax, P V) they land late:
+    // 2374 cycles.
+    const char* kb = reinterpret_cast<const char*>(kbuf(st));
+    u32x4 kf[DS];
+#pragma unroll
+    for (int s2 = 0; s2 < DS; ++s2) kf[s2] = *reinterpret_cast<const u32x4*>(kb + koff[s2]);
     f32x16 sacc = f32x16{};
-    const char* kb = reinterpret_cast<const char*>(kbuf(st)) + krow * RB;
-    // In 64-row workgroups the MFMA bursts run at raised wave priority, so that
+    // In 64-row workgroups the score MFMAs run at raised wave priority, so that
     // a wave issuing them is not held back by the softmax work of the other
     // wave on its SIMD (which belongs to the other workgroup, at another point
     // of its step).  The two waves a SIMD holds of an 8-wave workgroup are at
-    // the same point of the same step, and run faster without it.
+    // the same point of the same step, and do as well without it.
     if (kPrio) __builtin_amdgcn_s_setprio(2);
 #pragma unroll
     for (int s2 = 0; s2 < DS; ++s2) {
-      const u32x4 a = *reinterpret_cast<const u32x4*>(kb + 16 * ((2 * s2 + g) ^ ksw));
-      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), qf[s2], sacc,
+      sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[s2]), qf[s2], sacc,
                                                      0, 0, 0);
+      if (MORE) {
+        static_assert(2 * U <= DS, "at most one gather per score MFMA");
+        if (s2 % (DS / (2 * U)) == 0) {
+          const int n = s2 / (DS / (2 * U));
+          __builtin_amdgcn_sched_barrier(0);
+          gather(n, st ^ 1);
+          if (n == 2 * U - 1) load_ids(t + 2);  // past the list these read 0
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
     }
     if (kPrio) __builtin_amdgcn_s_setprio(0);
     // The V^T operands (transposing LDS reads) are fetched now, so that their
@@ -343,27 +413,23 @@ __global__ __launch_bounds__(4 * ROWS) void k_sparse_attn(
     const char* vb = reinterpret_cast<const char*>(vbuf(st));
     i16x8 vfrag[DB][2];
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      const int d = 32 * db + 16 * vhalf + 4 * tp;  // first of the 4 head-dim values addressed
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        const int k0 = 32 * kw + 16 * ks + 4 * g + tq;  // key row this lane addresses
-        const int k1 = k0 + 8;
-        const char* a0 = vb + k0 * RB + 16 * ((d >> 3) ^ swz<D>(k0)) + 8 * ((d >> 2) & 1);
-        const char* a1 = vb + k1 * RB + 16 * ((d >> 3) ^ swz<D>(k1)) + 8 * ((d >> 2) & 1);
+        const char* a0 = vb + voff[db][0] + 16 * ks * RB;  // the swizzle repeats every 16 rows
+        const char* a1 = vb + voff[db][1] + 16 * ks * RB;
         const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(i16x4, a0));
         const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(i16x4, a1));
         vfrag[db][ks] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
       }
-    }
 
     // Masks are needed only on the list's last tile and, when causal, on tiles
     // reaching past this wave's first row (lists are ascending).
     const int tbase = tile_of(t) * kTile;
     const int nvalid = min(kTile, count - tbase);
     const int32_t* ids = ibuf(st);
-    const bool need_mask = nvalid < kTile || (causal && ids[nvalid - 1] > row0 + 32 * rw);
-    if (need_mask) {
+    if (nvalid < kTile ||
+        (causal && __builtin_amdgcn_readfirstlane(ids[nvalid - 1]) > row0 + 32 * rw)) {
 #pragma unroll
       for (int m4 = 0; m4 < 4; ++m4) {
         const int kl = 32 * kw + 8 * m4 + 4 * g;
@@ -377,64 +443,102 @@ __global__ __launch_bounds__(4 * ROWS) void k_sparse_attn(
         }
       }
     }
-    // Lazy rescaling: x = s * scale - m_run (log2 units) is what exp2 needs
-    // anyway, and the weights 2^x are computed first.  Their tile sum (of the
-    // fp32 weights, before the bf16 rounding of the ones that enter P V, so
-    // that the normaliser and the LSE carry no bf16 error) bounds every
-    // weight, so a sum <= 256 on all lanes shows that no weight exceeds 256
-    // (harmless in bf16 / fp32) and the reference m_run stays.  Otherwise (a new maximum, or
-    // m_run = -inf: nothing seen yet) the rows whose maximum grew by more than
-    // 8 move their reference, O and l are rescaled, and the weights are
-    // recomputed.
-    float x[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) x[e] = __builtin_fmaf(sacc[e], scale_log2, -m_run);
-    bf16x8 pb0, pb1;
-    auto weights = [&]() __attribute__((always_inline)) {
-      f32x8 pf[2];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) pf[e >> 3][e & 7] = __builtin_amdgcn_exp2f(x[e]);
-      pb0 = __builtin_convertvector(pf[0], bf16x8);
-      pb1 = __builtin_convertvector(pf[1], bf16x8);
-      // a tree of fp32 adds (short dependency chains)
-      float s4[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) s4[i] = (pf[0][i] + pf[0][i + 4]) + (pf[1][i] + pf[1][i + 4]);
-      return (s4[0] + s4[1]) + (s4[2] + s4[3]);
-    };
-    float tsum = weights();
-    if (__any(!(tsum <= 256.0f))) {
+    // References.  Until every row of the wave has met a visible key (usually
+    // after the first tile), and throughout a careful walk, rows whose maximum
+    // grew by more than 8 (log2 units) move their reference before the weights
+    // are computed, and O and l are rescaled.
+    if (!settled) {
       float tmax = kNegInf;
 #pragma unroll
       for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, sacc[e]);
       tmax = wave_max_xor32(tmax);
       const float m_new = fmaxf(m_run, tmax * scale_log2);
       const float m_ref = (m_new > m_run + 8.0f) ? m_new : m_run;
-      const float alpha = __builtin_amdgcn_exp2f(m_run - (m_ref == kNegInf ? 0.0f : m_ref));
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
       l_run *= alpha;
 #pragma unroll
       for (int db = 0; db < DB; ++db) oacc[db] *= alpha;
       m_run = m_ref;
-      const float m_sub = m_run == kNegInf ? 0.0f : m_run;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) x[e] = __builtin_fmaf(sacc[e], scale_log2, -m_sub);
-      tsum = weights();
+      settled = __builtin_amdgcn_readfirstlane(!careful && !__any(m_run == kUnseen));
     }
+    // Weights 2^x, x = s * scale - m_run (log2 units), and O^T += V_tile^T P^T
+    // in one run of code: the second half's exponentials run beside the first
+    // half's MFMAs.  The normaliser sums the fp32 weights, before the bf16
+    // rounding of the ones that enter P V, so that it and the LSE carry no bf16
+    // error.
+    float x[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = __builtin_fmaf(sacc[e], scale_log2, -m_run);
+    f32x8 pf[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pf[ks][e] = __builtin_amdgcn_exp2f(x[8 * ks + e]);
+      const bf16x8 pb = __builtin_convertvector(pf[ks], bf16x8);
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+        oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vfrag[db][ks]),
+                                                           pb, oacc[db], 0, 0, 0);
+    }
+    float s4[4];  // a tree of fp32 adds (short dependency chains)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s4[i] = (pf[0][i] + pf[0][i + 4]) + (pf[1][i] + pf[1][i + 4]);
+    const float tsum = (s4[0] + s4[1]) + (s4[2] + s4[3]);
     l_run += tsum;
-
-    // O^T += V_tile^T P^T.
-    if (kPrio) __builtin_amdgcn_s_setprio(2);
+    // Weights above 256 (a sum <= 256 on every lane rules them out) went into O
+    // and l as they are, exact in bf16 and fp32 range; the reference moves up
+    // by a power of two now, for the tiles to come.  A weight past fp32 range
+    // leaves l or O infinite, which the end of the walk sees.
+    if (__any(!(tsum <= 256.0f))) {
+      const float top = wave_max_xor32(tsum);
+      const int up = top > 256.0f ? __builtin_amdgcn_frexp_expf(top) : 0;
+      const float alpha = __builtin_amdgcn_ldexpf(1.0f, -up);
+      l_run *= alpha;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) oacc[db] *= alpha;
+      m_run += static_cast<float>(up);
+    }
+  };
+  // The walk, at most twice: a score more than ~119 (log2 units) above its
+  // row's reference overflows a weight, which a test of every weight before
+  // P V would catch in time (as the first tile does) at the price of the
+  // softmax running beside no MFMA.  So O and l are tested once, at the end:
+  // anything not finite in the workgroup sends all of it through the list
+  // again with the references fixed before the weights.
+  for (;;) {
+    if (ntiles > 0) {
+      load_ids(0);
+#pragma unroll
+      for (int n = 0; n < 2 * U; ++n) gather(n, 0);
+      stage_ids(0, 0);
+      load_ids(1);
+    }
+    int t = 0;
+    for (; t + 2 < ntiles; t += 2) {
+      step(t, 0, std::true_type{});
+      step(t + 1, 1, std::true_type{});
+    }
+    if (t + 1 < ntiles) {
+      step(t, 0, std::true_type{});
+      step(t + 1, 1, std::false_type{});
+    } else if (t < ntiles) {
+      step(t, 0, std::false_type{});
+    }
+    if (careful) break;
+    float fin = l_run * 0.0f;  // 0, or NaN once anything is not finite
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-        oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vfrag[db][ks]),
-                                                           ks ? pb1 : pb0, oacc[db], 0, 0, 0);
-    if (kPrio) __builtin_amdgcn_s_setprio(0);
-  };
-  for (int t = 0; t < ntiles; t += 2) {
-    step(t, 0);
-    if (t + 1 < ntiles) step(t + 1, 1);
+      for (int e = 0; e < 16; ++e) fin = __builtin_fmaf(oacc[db][e], 0.0f, fin);
+    if (__any(fin != 0.0f) && lane == 0) s_redo = 1;
+    __syncthreads();
+    if (!__builtin_amdgcn_readfirstlane(s_redo)) break;
+    careful = 1;
+    settled = 0;
+    m_run = kUnseen;
+    l_run = 0.0f;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[db] = f32x16{};
   }
 
   if (herd && wave == 0 && lane == 0 && ntiles % kHerdBatch != 0)
@@ -463,7 +567,7 @@ __global__ __launch_bounds__(4 * ROWS) void k_sparse_attn(
   const float l1 = red_ml[64 + lane];
   const float m = fmaxf(m_run, m1);
   float a0 = 0.0f, a1 = 0.0f, inv = 0.0f, l = 0.0f;
-  if (m != kNegInf) {
+  if (m != kUnseen) {
     a0 = __builtin_amdgcn_exp2f(m_run - m);
     a1 = __builtin_amdgcn_exp2f(m1 - m);
     l = a0 * l_run + a1 * l1;

@@ -294,3 +294,32 @@ def test_causal_attention_is_deterministic(gpu):
         again, lse2 = va.sparse_attn(q, k, v, ti, tc, P, True, return_lse=True, order=o)
         assert torch.equal(again.view(torch.int16), first.view(torch.int16))
         assert torch.equal(lse1, lse2)
+
+
+@pytest.mark.parametrize("step", [4.0, 60.0, 110.0])
+@pytest.mark.parametrize("N,D,P,causal", [(64, 128, 64, False), (128, 64, 64, True), (192, 128, 128, True),
+                                          (400, 128, 64, False), (400, 64, 128, True), (500, 128, 128, False)])
+def test_references_that_move_after_the_weights(gpu, N, D, P, causal, step):
+    """Scores rise by `step` nats from one 64-key tile to the next: by less than a weight's
+    range (references move after a tile), past it (weights overflow and the list is walked
+    again with references fixed first), and in lists of 1 to 8 tiles (odd, even, ragged ends).
+    LSE: the scaled maximum (up to 7 x 110 x 1.443 = 1111) is rounded to fp32 three times
+    (product, reference, difference), 3 x 1111 x 2^-24 = 2e-4, the rest as above."""
+    r = np.random.Generator(np.random.PCG64(int(N + D + step)))
+    u = r.standard_normal(D)
+    u /= np.linalg.norm(u)
+    q = (math.sqrt(D) * u + 0.02 * r.standard_normal((1, 2, N, D))).astype(np.float32)
+    k = 0.02 * r.standard_normal((1, 1, N, D)) + (step * (np.arange(N) // 64))[:, None] * u
+    qb, kb = synth.to_bf16_bits(q), synth.to_bf16_bits(k.astype(np.float32))
+    vb = synth.random_bits(5, (1, 1, N, D))
+    Np = (N + P - 1) // P
+    idx, cnt = random_lists(9, 1, 2, Np, N, P, causal, N, N, min_count=N)
+    o_ref, lse_ref = oracle.sparse_attn(qb, kb, vb, idx, cnt, P, causal)
+    o, lse = va.sparse_attn(dev(qb), dev(kb), dev(vb), torch.from_numpy(idx).cuda(),
+                            torch.from_numpy(cnt).cuda(), P, causal, return_lse=True)
+    torch.cuda.synchronize()
+    got = o.float().cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    err = np.abs(got - o_ref)
+    assert err.max() <= ATOL_MAX and err.mean() <= ATOL_MEAN, (err.max(), err.mean())
+    assert np.abs(lse.cpu().numpy().astype(np.float64) - lse_ref).max() <= 3e-4
