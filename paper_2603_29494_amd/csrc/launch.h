@@ -64,8 +64,21 @@ struct SelectArgs {
 constexpr size_t kStaticWorkspaceBytes = size_t(64) << 20;
 hipError_t static_workspace(void** ptr);
 
+// Selection of short sequences (select_short.hip): whether a call may take it,
+// the least workspace it needs (one row tile's scores), and the workspace it
+// makes use of.
+constexpr int64_t kShortMaxN = 16384;
+bool short_select_ok(int64_t N, int32_t mode);
+size_t short_select_min_bytes(int64_t B, int64_t Hq, int64_t N, int64_t D, int32_t block);
+size_t short_select_bytes(int64_t B, int64_t Hq, int64_t N, int64_t D, int32_t block);
+hipError_t launch_select_short(const SelectArgs& a, hipStream_t stream);
+
+// Workspace the size query reports, and the least that a call accepts (a short
+// sequence fits either kind of selection, so the smaller of the two).
 size_t select_workspace_bytes(int64_t B, int64_t Hq, int64_t Hkv, int64_t N, int64_t D,
                               int32_t block, int32_t mode, int64_t cap);
+size_t select_min_workspace_bytes(int64_t B, int64_t Hq, int64_t Hkv, int64_t N, int64_t D,
+                                  int32_t block, int32_t mode);
 hipError_t launch_select(const SelectArgs& a, hipStream_t stream);
 
 // Rows whose list breaks the attention's input contract, counted into *n_bad

@@ -34,10 +34,12 @@
 // read from a copy in MFMA operand order that each call writes once.
 #include <float.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.h"
 #include "launch.h"
+#include "select_common.h"
 
 namespace vecattn {
 namespace {
@@ -53,14 +55,12 @@ constexpr int kSampleBins = 256;  // bins of the sampled-score histogram that pl
 // bin, so neither field can carry into the other.
 constexpr int kMassShift = 48;
 constexpr double kMassUnit = 0x1p-31;
-constexpr float kTopPRange = 40.0f;  // nats below the row maximum the level-0 topP bins span
 // topP cut bins are resolved to this share of the row's total mass: the GPU's
 // fp32 scores and exp2 already differ from exact masses by ~1e-7 relative.
 constexpr double kTopPMassSlack = 0x1p-20;
 constexpr int kLevels = 6;      // histogram refinements per round (idle ones cost ~6 us)
 constexpr int kCand = 1024;     // candidate capacity per row
 constexpr int kRounds = 2;      // a topP row whose count exceeds cap reruns as topK(cap)
-constexpr int kMaxHeadParams = 128;  // query heads a per-head parameter list may cover
 // Rows entering each later pass are counted (nact[level] for histogram level
 // >= 1, nact[kEmitSlot] for the emit pass); a pass that no row needs returns
 // at once, without reading row state.
@@ -151,36 +151,9 @@ struct SelParams {
   int64_t per_xcd;  // work items per XCD
 };
 
-__device__ __forceinline__ uint32_t ord_key(float f) {
-  const uint32_t u = __float_as_uint(f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-__device__ __forceinline__ float ord_val(uint32_t k) {
-  return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
-}
-
 // The selection parameter of a row (rows are ordered (b, h, i)).
 __device__ __forceinline__ double row_param(const SelParams& p, int64_t row) {
   return p.per_head ? p.head_param[(row / p.Np) % p.Hq] : p.param;
-}
-
-__device__ __forceinline__ int eligible(int i, int P, int N, int causal) {
-  return causal ? min(N, (i + 1) * P) : N;
-}
-
-__device__ __forceinline__ int topk_count(double r, int L) {
-  int k = static_cast<int>(ceil(r * static_cast<double>(L) - 1e-9));
-  return min(max(k, 1), L);
-}
-
-// exp(tau * s - ref) for topP masses (s a raw score): exp2 in fp32 while the
-// exponent is in range (relative error ~1e-7), with an exact power-of-two
-// rescale below it.
-__device__ __forceinline__ double mass_term(float s, float tau, double ref) {
-  const double y = (static_cast<double>(s) * static_cast<double>(tau) - ref) * 1.4426950408889634;
-  if (y > -120.0) return static_cast<double>(__builtin_amdgcn_exp2f(static_cast<float>(y)));
-  const double n = floor(y);
-  return ldexp(static_cast<double>(__builtin_amdgcn_exp2f(static_cast<float>(y - n))), static_cast<int>(n));
 }
 
 // Key of a 32-key block that the operand-order copy of K places in A-operand
@@ -1214,20 +1187,6 @@ __global__ __launch_bounds__(256) void k_tiled_init(SelParams p) {
   s.phase = PH_EMIT;
 }
 
-// Inclusive prefix sum over the 64 lanes of a wave with DPP moves (no LDS):
-// shifts by 1, 2, 4, 8 inside each 16-lane row, then row 0's total into row 1
-// and row 2's into row 3 (broadcast of lane 15), and rows 0-1's total into
-// rows 2-3 (broadcast of lane 31).  Lanes without a source add 0.
-__device__ __forceinline__ int wave_incl_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
-  return x;
-}
-
 // ---------------------------------------------------------------------------
 // Resolve after a HIST pass: one wave per row.
 // ---------------------------------------------------------------------------
@@ -1539,16 +1498,6 @@ __global__ __launch_bounds__(256) void k_resolve_cand(SelParams p) {
 // loads do not wait for one another.
 constexpr int kCompactBatch = 8;
 
-// Orders this wave's LDS accesses on either side (a one-wave workgroup needs
-// no barrier).  Unlike __syncthreads() it does not wait for the wave's
-// global loads and stores: the prefetched bitmask words stay in flight and
-// the stores of the lists are not waited for.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __global__ __launch_bounds__(64) void k_compact(SelParams p) {
   const int64_t r = blockIdx.x;
   const RowState& s = p.st[r];
@@ -1726,9 +1675,16 @@ int choose_split(int64_t B, int64_t Hq, int64_t N, int32_t P) {
 
 size_t select_workspace_bytes(int64_t B, int64_t Hq, int64_t Hkv, int64_t N, int64_t D,
                               int32_t block, int32_t mode, int64_t cap) {
-  (void)mode;
   (void)cap;
+  if (short_select_ok(N, mode)) return short_select_bytes(B, Hq, N, D, block);
   return layout(B, Hq, Hkv, N, D, block, choose_split(B, Hq, N, block), mode == 1).total;
+}
+
+size_t select_min_workspace_bytes(int64_t B, int64_t Hq, int64_t Hkv, int64_t N, int64_t D,
+                                  int32_t block, int32_t mode) {
+  const size_t passes = layout(B, Hq, Hkv, N, D, block, choose_split(B, Hq, N, block), mode == 1).total;
+  if (!short_select_ok(N, mode)) return passes;
+  return std::min(passes, short_select_min_bytes(B, Hq, N, D, block));
 }
 
 template <int MODE>
@@ -1743,6 +1699,9 @@ void score_pass(int64_t D, bool topp, dim3 grid, const SelParams& p, hipStream_t
 }
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
+  if (short_select_ok(a.q.N, a.mode) &&
+      a.workspace_bytes >= short_select_min_bytes(a.q.B, a.q.H, a.q.N, a.q.D, a.block))
+    return launch_select_short(a, stream);
   const int64_t B = a.q.B, Hq = a.q.H, Hkv = a.k.H, N = a.q.N, D = a.q.D;
   const int32_t P = a.block;
   const int64_t Np = (N + P - 1) / P;

@@ -47,24 +47,6 @@ constexpr int kHerdBatch = 16;
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef short i16x8 __attribute__((ext_vector_type(8)));
-#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
-
-
-// Chunk swizzle: 16-byte chunk c of row r lives at chunk c ^ swz(r).  LDS has
-// 64 banks of 4 bytes; a 16-byte read serves 16 lanes per cycle, an 8-byte
-// read 32.  K reads (16 lanes = 16 consecutive rows, one logical chunk) need
-// swz to separate the rows that share banks: a bijection on r % 16 for
-// 256-byte rows, on (r / 2) % 8 for 128-byte rows (two rows per bank line).
-// Transposing V reads (32 lanes = 4 consecutive rows x 4 chunks x 2 halves)
-// need the row's contribution to move whole groups of 4 chunks: r % 4 drives
-// bits 2-3 (D = 128), or r / 2 % 2 drives bit 2 across the rows that share
-// banks (D = 64).  Both read patterns are then free of bank conflicts.
-template <int D>
-__host__ __device__ __forceinline__ constexpr int swz(int r) {
-  if constexpr (D == 128) return ((r & 3) << 2) | ((r >> 2) & 3);
-  else return (((r >> 1) & 1) << 2) | ((r >> 2) & 3);
-}
-
 // 16-byte copy per lane from a buffer (byte offset voff) to LDS (destination:
 // wave-uniform base + 16 * lane).  The 16-byte form exists only on gfx950;
 // the host pass of the compiler rejects it, so it is compiled for the device
@@ -90,13 +72,6 @@ __device__ __forceinline__ void ids_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t
 template <int U>
 __device__ __forceinline__ int row_bcast(int x) {
   return __builtin_amdgcn_update_dpp(0, x, 0x150 + U, 0xf, 0xf, true);
-}
-
-// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
 // SAME_STRIDE: K and V rows have the same stride, so a gathered row's K and V

@@ -157,7 +157,7 @@ vecattn_status select_check(const void* q, const vecattn_tdesc* qd, const void* 
   if ((causal & kKeepDiag) && mode != VECATTN_SEL_TOPK &&
       cap < max_count(qd->N, block, causal, mode, param))
     return VECATTN_ERR_CAPACITY;
-  *need = vecattn::select_workspace_bytes(qd->B, qd->H, kd->H, qd->N, qd->D, block, mode, cap);
+  *need = vecattn::select_min_workspace_bytes(qd->B, qd->H, kd->H, qd->N, qd->D, block, mode);
   return VECATTN_OK;
 }
 
@@ -419,7 +419,7 @@ vecattn_status vecattn_select_varlen(const void* q, const vecattn_tdesc* qd, con
     if ((mode == VECATTN_SEL_TOPK || (causal & kKeepDiag)) &&
         cap < max_count(n, block, causal, mode, param))
       return VECATTN_ERR_CAPACITY;
-    const size_t need = vecattn::select_workspace_bytes(1, qd->H, kd->H, n, qd->D, block, mode, cap);
+    const size_t need = vecattn::select_min_workspace_bytes(1, qd->H, kd->H, n, qd->D, block, mode);
     if (need > 0 && (!workspace || workspace_bytes < need)) return VECATTN_ERR_CAPACITY;
   }
   int64_t blocks = 0;  // blocks of the sequences before s
