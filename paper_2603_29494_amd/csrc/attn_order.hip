@@ -23,59 +23,113 @@
 namespace vecattn {
 namespace {
 
-constexpr int kOrderThreads = 1024;
+// Signature of a list: its mean key position in 512ths of N, from 8 entries.
+__device__ __forceinline__ int64_t sample(const int32_t* list, int64_t c, int j, int64_t N) {
+  const int64_t x = list[((2 * j + 1) * c) / 16];
+  return std::min<int64_t>(std::max<int64_t>(x, 0), N - 1);  // N <= 2^30: 8 of them fit
+}
+__device__ __forceinline__ int signature(int64_t sum, int64_t N) {
+  return static_cast<int>(std::min<int64_t>((sum * 64) / N, 511));  // mean * 512 / N
+}
 
-__global__ __launch_bounds__(kOrderThreads) void k_attn_order(
+// The signatures of all blocks, into the order array (each head's sort reads
+// its own before it writes them): eight lanes per block, over the whole chip.
+// The sampled entries are one cache line each, and a head's sort alone on its
+// CU waited for 16384 of them at 2048 blocks: 68 us of sort then, 50 at 1182
+// blocks, 16 at 512.  Heads of fewer than kSigBlocks blocks sample in the sort.
+constexpr int kSigBlocks = 256;
+__global__ __launch_bounds__(256) void k_signatures(const int32_t* __restrict__ idx, int64_t cap,
+                                                    const int32_t* __restrict__ counts, int64_t n,
+                                                    int64_t N, int32_t* __restrict__ order) {
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int64_t r = t >> 3;
+  if (r >= n) return;  // whole groups of eight lanes
+  const int64_t c = std::min<int64_t>(std::max<int64_t>(counts[r], 0), cap);
+  int64_t sum = c > 0 ? sample(idx + r * cap, c, static_cast<int>(t & 7), N) : 0;
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) sum += __shfl_xor(static_cast<long long>(sum), o);
+  if ((t & 7) == 0) order[r] = signature(sum, N);
+}
+
+// Bitonic sort of n2 = T * E keys, T threads with E consecutive ones each in
+// registers: exchanges over a distance below E happen inside a thread, below
+// 64 E inside a wave (lane exchanges), and only those further apart go through
+// LDS and a barrier: 10 of the 66 steps at 2048 keys (all of them: 11 us more).
+template <int E>
+__global__ __launch_bounds__(1024) void k_attn_order(
     const int32_t* __restrict__ idx, int64_t cap, const int32_t* __restrict__ counts, int32_t Np,
-    int64_t N, int32_t* __restrict__ order) {
+    int64_t N, int32_t sampled, int32_t* order) {
+  extern __shared__ uint64_t s_key[];  // [E][T]
   const int64_t bh = blockIdx.x;
-  const int tid = threadIdx.x;
-  __shared__ uint64_t key[kOrderMaxBlocks];
+  const int tid = threadIdx.x, T = blockDim.x, n2 = T * E;
   for (int64_t seg = 0; seg < Np; seg += kOrderMaxBlocks) {
     const int ns = static_cast<int>(std::min<int64_t>(Np - seg, kOrderMaxBlocks));
     const int32_t* cnt = counts + bh * Np + seg;
     int32_t* out = order + bh * Np + seg;
-    int n2 = 2;
-    while (n2 < ns) n2 <<= 1;
-    __syncthreads();  // the previous segment's keys have been written out
-    for (int i = tid; i < n2; i += kOrderThreads) {
+    uint64_t key[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      // Keys are made by thread i % T (neighbouring lists side by side) and
+      // sorted wherever they start.
+      const int i = e * T + tid;
       uint64_t kk = ~uint64_t(0);  // padding sorts last
       if (i < ns) {
         const int64_t c = std::min<int64_t>(std::max<int64_t>(cnt[i], 0), cap);
-        const int32_t* list = idx + (bh * Np + seg + i) * cap;
-        int64_t sum = 0;  // of 8 entries in [0, N), N <= 2^30
-        if (c > 0) {
+        uint64_t sig = 0;
+        if (sampled) {
+          sig = static_cast<uint64_t>(out[i]);
+        } else if (c > 0) {
+          const int32_t* list = idx + (bh * Np + seg + i) * cap;
+          int64_t sum = 0;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int64_t e = list[((2 * j + 1) * c) / 16];
-            sum += std::min<int64_t>(std::max<int64_t>(e, 0), N - 1);
-          }
+          for (int j = 0; j < 8; ++j) sum += sample(list, c, j, N);
+          sig = static_cast<uint64_t>(signature(sum, N));
         }
-        // mean * 512 / N = sum * 64 / N, below 512
-        const uint64_t sig = static_cast<uint64_t>(std::min<int64_t>((sum * 64) / N, 511));
         kk = (static_cast<uint64_t>((int64_t(1) << 30) - c) << 33) | (sig << 24) |
              static_cast<uint64_t>(i);
       }
-      key[i] = kk;
+      key[e] = kk;
     }
-    __syncthreads();
-    // Bitonic sort of n2 keys, ascending.
+    // Element i = tid * E + e; ascending runs where i & k is 0.
+    auto keep = [&](int e, uint64_t other, int j, int k) __attribute__((always_inline)) {
+      const int i = tid * E + e;
+      const bool low = ((i & j) == 0) == ((i & k) == 0);
+      key[e] = low ? std::min(key[e], other) : std::max(key[e], other);
+    };
     for (int k = 2; k <= n2; k <<= 1) {
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        for (int t = tid; t < n2 / 2; t += kOrderThreads) {
-          const int a = (t / j) * 2 * j + (t % j);
-          const int b = a + j;
-          const uint64_t x = key[a], y = key[b];
-          if ((x > y) == ((a & k) == 0)) {
-            key[a] = y;
-            key[b] = x;
-          }
-        }
+      int j = k >> 1;
+      for (; j >= 64 * E; j >>= 1) {
+        __syncthreads();  // the exchange before has been read
+#pragma unroll
+        for (int e = 0; e < E; ++e) s_key[e * T + tid] = key[e];
         __syncthreads();
+#pragma unroll
+        for (int e = 0; e < E; ++e) keep(e, s_key[e * T + (tid ^ (j / E))], j, k);
+      }
+      for (; j >= E; j >>= 1) {
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+          keep(e, __shfl_xor(static_cast<unsigned long long>(key[e]), j / E), j, k);
+      }
+#pragma unroll
+      for (int jj = E / 2; jj > 0; jj >>= 1) {
+        if (jj > j) continue;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          if (e & jj) continue;
+          const uint64_t x = key[e], y = key[e | jj];
+          const bool up = ((tid * E + e) & k) == 0;
+          key[e] = up ? std::min(x, y) : std::max(x, y);
+          key[e | jj] = up ? std::max(x, y) : std::min(x, y);
+        }
       }
     }
-    for (int i = tid; i < ns; i += kOrderThreads)
-      out[i] = static_cast<int32_t>(seg + static_cast<int64_t>(key[i] & 0xFFFFFF));
+    __syncthreads();  // every signature has been read
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = tid * E + e;
+      if (i < ns) out[i] = static_cast<int32_t>(seg + static_cast<int64_t>(key[e] & 0xFFFFFF));
+    }
   }
 }
 
@@ -84,9 +138,26 @@ __global__ __launch_bounds__(kOrderThreads) void k_attn_order(
 hipError_t launch_attn_order(const int32_t* idx, int64_t cap, const int32_t* counts, int64_t rows,
                              int32_t Np, int64_t N, int32_t* order, hipStream_t stream) {
   if (rows == 0 || Np == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_attn_order, dim3(static_cast<unsigned>(rows)), dim3(kOrderThreads), 0,
-                     stream, idx, cap, counts, Np, N, order);
-  return hipGetLastError();
+  int n2 = 64;  // one wave at least
+  while (n2 < std::min(Np, kOrderMaxBlocks)) n2 <<= 1;
+  const int each = std::max(1, n2 / 1024);
+  const int64_t blocks = rows * Np;
+  const int sampled = Np >= kSigBlocks && (blocks + 31) / 32 <= INT32_MAX;
+  if (sampled)
+    hipLaunchKernelGGL(k_signatures, dim3(static_cast<unsigned>((blocks + 31) / 32)), dim3(256), 0,
+                       stream, idx, cap, counts, blocks, N, order);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(rows)), dim3(n2 / each), n2 * 8, stream,
+                       idx, cap, counts, Np, N, sampled, order);
+    return hipGetLastError();
+  };
+  switch (each) {
+    case 1: return run(k_attn_order<1>);
+    case 2: return run(k_attn_order<2>);
+    case 4: return run(k_attn_order<4>);
+    case 8: return run(k_attn_order<8>);
+    default: return run(k_attn_order<16>);
+  }
 }
 
 }  // namespace vecattn

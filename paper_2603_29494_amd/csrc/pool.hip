@@ -1,24 +1,32 @@
 // Query pooling, paper Eq. 2 (Sec. 3.1.1): the pooled query of a block is the
-// mean of the block's query rows.  One thread owns 8 consecutive head-dim
-// values of one block, sums the block's rows in fp64 in row order (bf16 values
+// mean of the block's query rows.  A thread owns 8 consecutive head-dim values
+// of one block and every RG-th of its rows, sums them in fp64 (bf16 values
 // have 8 significant bits, so these sums are exact unless the values span more
-// than ~2^38 in magnitude) and rounds the mean to bf16 once.
+// than ~2^38 in magnitude), adds the RG partial sums and rounds the mean to
+// bf16 once.
 #include "device_common.h"
 #include "launch.h"
 
 namespace vecattn {
 namespace {
 
+// RG = 64 / (D / 8): one wave per block, a load instruction covering whole
+// rows (1 KB in a row of memory) and four or eight times the waves of RG = 1
+// (one thread per chunk), which small blocks keep.  Bound by the read of Q from
+// 17k tokens on; below by the chain of a thread's loads.  RG = 1 / 64 rows per
+// block: 1k tokens 7.2 us, 4 x 4k 10.0, 32k (28 heads) 52.8.
+template <int D, int RG>
 __global__ __launch_bounds__(256) void k_pool(const uint16_t* __restrict__ q, int64_t q_sB,
                                               int64_t q_sH, int64_t q_sN, int32_t H, int32_t N,
-                                              int32_t D, int32_t P, int32_t Np,
-                                              uint16_t* __restrict__ qp, int64_t p_sB,
-                                              int64_t p_sH, int64_t p_sN, int64_t total) {
+                                              int32_t P, int32_t Np, uint16_t* __restrict__ qp,
+                                              int64_t p_sB, int64_t p_sH, int64_t p_sN,
+                                              int64_t total) {
+  constexpr int CH = D / 8;
   const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= total) return;
-  const int chunks = D / 8;
-  const int c = static_cast<int>(t % chunks);
-  int64_t rest = t / chunks;
+  if (t >= total) return;  // whole waves with RG > 1
+  const int c = static_cast<int>(t % CH);
+  const int rg = static_cast<int>(t / CH % RG);
+  int64_t rest = t / (CH * RG);
   const int i = static_cast<int>(rest % Np);
   rest /= Np;
   const int h = static_cast<int>(rest % H);
@@ -37,17 +45,23 @@ __global__ __launch_bounds__(256) void k_pool(const uint16_t* __restrict__ q, in
     }
   };
   // Eight rows are loaded before any is summed, so that a thread keeps eight
-  // loads in flight; the sums still run in row order.
-  int r = r0;
-  for (; r + 8 <= r1; r += 8) {
+  // loads in flight.
+  int r = r0 + rg;
+  for (; r + 7 * RG < r1; r += 8 * RG) {
     u32x4 w[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      w[j] = *reinterpret_cast<const u32x4*>(base + static_cast<int64_t>(r + j) * q_sN);
+      w[j] = *reinterpret_cast<const u32x4*>(base + static_cast<int64_t>(r + j * RG) * q_sN);
 #pragma unroll
     for (int j = 0; j < 8; ++j) add_row(w[j]);
   }
-  for (; r < r1; ++r) add_row(*reinterpret_cast<const u32x4*>(base + static_cast<int64_t>(r) * q_sN));
+  for (; r < r1; r += RG)
+    add_row(*reinterpret_cast<const u32x4*>(base + static_cast<int64_t>(r) * q_sN));
+#pragma unroll
+  for (int o = CH; o < CH * RG; o <<= 1)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], o);
+  if (rg != 0) return;
   const double n = static_cast<double>(r1 - r0);
   u32x4 out;
 #pragma unroll
@@ -64,14 +78,21 @@ __global__ __launch_bounds__(256) void k_pool(const uint16_t* __restrict__ q, in
 hipError_t launch_pool(const Tensor4& q, int32_t block, void* qp, int64_t qp_sB, int64_t qp_sH,
                        int64_t qp_sN, hipStream_t stream) {
   const int32_t Np = static_cast<int32_t>((q.N + block - 1) / block);
-  const int64_t total = q.B * q.H * static_cast<int64_t>(Np) * (q.D / 8);
+  // Several row groups pay from a few rows each; blocks of fewer than 32 rows
+  // would leave most of a wave without work.
+  const bool split = block >= 32;
+  const int chunks = static_cast<int>(q.D / 8);
+  const int64_t total = q.B * q.H * static_cast<int64_t>(Np) * (split ? 64 : chunks);
   if (total == 0) return hipSuccess;
   const int threads = 256;
   const dim3 grid(static_cast<unsigned>((total + threads - 1) / threads));
-  hipLaunchKernelGGL(k_pool, grid, dim3(threads), 0, stream, static_cast<const uint16_t*>(q.ptr),
-                     q.sB, q.sH, q.sN, static_cast<int32_t>(q.H), static_cast<int32_t>(q.N),
-                     static_cast<int32_t>(q.D), block, Np, static_cast<uint16_t*>(qp), qp_sB,
-                     qp_sH, qp_sN, total);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, static_cast<const uint16_t*>(q.ptr),
+                       q.sB, q.sH, q.sN, static_cast<int32_t>(q.H), static_cast<int32_t>(q.N),
+                       block, Np, static_cast<uint16_t*>(qp), qp_sB, qp_sH, qp_sN, total);
+  };
+  if (q.D == 128) split ? run(k_pool<128, 4>) : run(k_pool<128, 1>);
+  else split ? run(k_pool<64, 8>) : run(k_pool<64, 1>);
   return hipGetLastError();
 }
 

@@ -69,6 +69,14 @@ def test_pool_bit_exact(gpu, N, P, D):
     assert np.array_equal(got, oracle.pool(q, P))
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("N,P", [(100, 31), (100, 32), (95, 33), (1000, 64), (33, 64), (1999, 1000)])
+def test_pool_row_groups_bit_exact(gpu, N, P, D):
+    """Both sides of the block size from which a wave shares a block's rows, and ragged ends."""
+    q = synth.random_bits(N + P, (2, 2, N, D), scale=3.0)
+    assert np.array_equal(host_bits(va.pool(dev(q), P)), oracle.pool(q, P))
+
+
 def test_pool_strided_input(gpu):
     q = synth.random_bits(7, (1, 100, 4, 64))        # [B, N, H, D] storage
     tq = dev(q).permute(0, 2, 1, 3)                    # logical [B, H, N, D]

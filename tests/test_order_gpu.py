@@ -94,6 +94,17 @@ def test_order_segments(gpu, Np):
         assert np.array_equal(np.sort(seg), np.arange(s0, s0 + len(seg)))
 
 
+@pytest.mark.parametrize("Np", [2, 64, 65, 128, 1024, 1025, 2049, 4097, 8193])
+def test_order_at_sort_sizes(gpu, Np):
+    """Both sides of the sizes where the sort changes its threads and keys per thread."""
+    r = np.random.Generator(np.random.PCG64(Np))
+    N, P, cap = Np, 1, 3
+    cnt = r.integers(0, 4, size=(1, 2, Np)).astype(np.int32)
+    idx = np.sort(r.integers(0, N, size=(1, 2, Np, cap)), axis=-1).astype(np.int32)
+    got = va.attn_order(cuda_i32(idx), cuda_i32(cnt), N, P).cpu().numpy()
+    assert np.array_equal(got, order_ref(idx, cnt, N, cap))
+
+
 def check_attn(o_gpu, lse_gpu, o_ref, lse_ref, label):
     o = o_gpu.float().cpu().numpy().astype(np.float64)
     err = np.abs(o - o_ref)
