@@ -65,6 +65,7 @@ constexpr int kRounds = 2;      // a topP row whose count exceeds cap reruns as 
 // >= 1, nact[kEmitSlot] for the emit pass); a pass that no row needs returns
 // at once, without reading row state.
 constexpr int kEmitSlot = kLevels + 1;
+constexpr int kRedoSlot = kLevels + 2;  // rows sent back for the second round
 constexpr int kActiveSlots = 16;
 
 enum Phase : int { PH_IDLE = 0, PH_HIST = 1, PH_COLLECT = 2, PH_DONE = 3, PH_EMIT = 4 };
@@ -75,26 +76,27 @@ enum Mode : int {
 };
 constexpr int kSampleStride = 16;  // 32-key blocks between sampled blocks
 
-struct RowState {
+// Row state.  The first 48 bytes are what the score passes read, as three
+// 16-byte loads per row; the rest belongs to the resolve steps.  Scores are raw
+// fp32 dot products <q_p, k_j> (the softmax scale tau > 0 preserves their order;
+// it enters only the topP masses).
+struct alignas(16) RowState {
   int phase;
-  int level;        // histogram level the next HIST pass runs
   int topp;         // 1: cut by mass, 0: cut by rank
-  int k_target;     // topK: number of keys to keep
+  int mins;         // 1: minS row before its count is known (level 0)
   int L;            // eligible keys
+  float s_lo, s_hi; // current interval: keys with s_lo <= s <= s_hi (exact float bounds)
+  float binv, badd; // bin of s: floor(fma(s, binv, badd)), badd = -blo * binv
+  float smax;       // topP: the row's largest score (ref = tau * smax)
+  float tstar;      // cut score
   int tie_partial;  // 1: only the first k_eq keys tied at t* are kept
+  int tie_interval; // 1: the keys tied at the cut are all those in [s_lo, s_hi]
+  int level;        // histogram level the next HIST pass runs
+  int k_target;     // topK: number of keys to keep
   int k_eq;         // keys tied at t* that are kept
   int count;        // final count
   int clamped;      // 1 if the threshold selection was clamped to cap
-  int tie_interval; // 1: the keys tied at the cut are all those in [s_lo, s_hi]
-  int mins;         // 1: minS row before its count is known (level 0)
-  int pad0;
-  // Scores below are raw fp32 dot products <q_p, k_j> (the softmax scale tau
-  // > 0 preserves their order; it enters only the topP masses).
-  float s_lo, s_hi; // current interval: keys with s_lo <= s <= s_hi (exact float bounds)
-  float blo, binv;  // bin range of the current level: lo and bins per unit
-  float badd;       // bin of s: floor(fma(s, binv, badd)), badd = -blo * binv
-  float smax;       // topP: the row's largest score (ref = tau * smax)
-  float tstar;      // cut score
+  float blo;        // bin range of the current level: lo (and binv bins per unit)
   double ref;       // softmax reference (an upper bound of the row's scores)
   double Z;         // total mass (topP)
   double pZ;        // p * Z
@@ -198,31 +200,39 @@ __device__ __forceinline__ void set_bins(RowState& s, float lo, float binv) {
   s.badd = -lo * binv;
 }
 
+// Smallest ordered key z in (a, z] for which `at_least` holds, over the wave: it
+// is monotone, false at a and true at z.  64 probes a round: 6 rounds for the
+// whole float range.
+template <typename P>
+__device__ __forceinline__ uint32_t wave_first(uint32_t a, uint32_t z, P at_least) {
+  const int lane = threadIdx.x & 63;
+  while (z - a > 1) {
+    const uint32_t step = (z - a + 63) / 64;
+    const uint32_t m = min(static_cast<uint64_t>(a) + static_cast<uint64_t>(lane + 1) * step,
+                           static_cast<uint64_t>(z));
+    const uint64_t hit = __ballot(m == z || at_least(ord_val(m)));
+    const int f = __builtin_ctzll(hit);
+    const uint32_t nz = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(m), f));
+    if (f > 0) a = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(m), f - 1));
+    z = nz;
+  }
+  return z;
+}
+
 // The interval after choosing bins [ba, bb] of the level with bin function
 // (mul, add) inside [s_lo, s_hi]: the bin function is monotone in s, so the
-// chosen set is again a float interval; its exact ends are found by binary
-// search over ordered float keys with the same bin function the passes use.
+// chosen set is again a float interval; its exact ends are found by search
+// over ordered float keys with the same bin function the passes use (all lanes
+// of the wave alike).
 __device__ __forceinline__ void narrow(float& s_lo, float& s_hi, float mul, float add, int ba, int bb,
                                        int nb) {
+  const uint32_t first = ord_key(-FLT_MAX), last = ord_key(FLT_MAX);
   // smallest s with bin >= ba
-  uint32_t a = ord_key(-FLT_MAX), z = ord_key(FLT_MAX);
-  if (bin_of(ord_val(a), mul, add, nb) < ba) {
-    while (z - a > 1) {
-      const uint32_t m = a + (z - a) / 2;
-      if (bin_of(ord_val(m), mul, add, nb) >= ba) z = m; else a = m;
-    }
-    s_lo = fmaxf(s_lo, ord_val(z));
-  }
-  // largest s with bin <= bb
-  a = ord_key(-FLT_MAX);
-  z = ord_key(FLT_MAX);
-  if (bin_of(ord_val(z), mul, add, nb) > bb) {
-    while (z - a > 1) {
-      const uint32_t m = a + (z - a) / 2;
-      if (bin_of(ord_val(m), mul, add, nb) <= bb) a = m; else z = m;
-    }
-    s_hi = fminf(s_hi, ord_val(a));
-  }
+  if (bin_of(-FLT_MAX, mul, add, nb) < ba)
+    s_lo = fmaxf(s_lo, ord_val(wave_first(first, last, [&](float x) { return bin_of(x, mul, add, nb) >= ba; })));
+  // largest s with bin <= bb: the one before the first with a higher bin
+  if (bin_of(FLT_MAX, mul, add, nb) > bb)
+    s_hi = fminf(s_hi, ord_val(wave_first(first, last, [&](float x) { return bin_of(x, mul, add, nb) > bb; }) - 1u));
 }
 
 // ---------------------------------------------------------------------------
@@ -359,25 +369,38 @@ __global__ __launch_bounds__(256) void k_kmax_init(float* kmax, int n) {
 // The scoring pass.  Work items are ordered (head, split, row tile) with the
 // row tile fastest and handed out XCD by XCD, so the row tiles of one head
 // that read the same key split run together on one XCD and share its L2.
-// ---------------------------------------------------------------------------
 // TOPP: the launch selects by mass (rows restarted as topK(cap) may be mixed
 // in); otherwise no mass is computed.
-// Histogram passes without per-bin masses (every level of topK / minS rows,
-// levels >= 1 of topP rows) are held to 168 VGPRs so that three waves share
-// each SIMD (their 33 KB of LDS allows it): the latency of the K loads and of the
-// MFMA chains is then hidden better (~5% of the selection at the 75k DiT layer).
+//
+// A block of 32 keys costs a wave 16 MFMAs (512 cycles), 130 to 200 vector
+// instructions and up to 32 LDS atomics (131 cycles of the CU's LDS).  COLLECT
+// and EMIT compute the scores of block n + 1 beside the work on block n's: two
+// accumulator pairs, taken in turn, each MFMA followed by a share of the other
+// pair's compares (scheduling-group hints), no branch between them; half by half
+// instead, COLLECT took 1978 us at the 75k DiT layer against 1565.  The
+// histogram and maximum passes work half by half at three waves per SIMD (168
+// registers): pipelined, at two, they were no faster (1318 against 1254 us).
+// The products leave lane (g, ln) with keys 16 g .. + 15 of row ln (first
+// accumulator) and row 32 + ln (second), and the work on the scores is done
+// there; a block's flags are exchanged between the half-waves as words, so that
+// each lane stores and lists the candidates of a row of its own (row `lane`).
+// (A half-wave swap takes 16 cycles: 16 of them per block, to give each lane
+// the scores of one row, cost 264.)
+// ---------------------------------------------------------------------------
 template <int D, int MODE, bool TOPP>
 __global__ __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu((MODE == MODE_HIST || (MODE == MODE_HIST0 && !TOPP)) ? 3 : 1)))
+__attribute__((amdgpu_waves_per_eu((MODE == MODE_HIST || (MODE == MODE_HIST0 && !TOPP)) ? 3 : 2)))
 void k_score_pass(SelParams p) {
   constexpr int DS = D / 16;
+  constexpr bool PIPE = MODE == MODE_COLLECT || MODE == MODE_EMIT;
   constexpr bool HIST = MODE == MODE_HIST || MODE == MODE_HIST0;
-  // Bin-major layout, entry (bin, row) at bin * kRowsWG + row: the 32 rows of
-  // a wave's update sit in 32 distinct banks whatever their bins (the two
-  // lanes of one row share a bank: at most 2-way conflicts; a row-major
-  // layout gave ~4-way ones from bins colliding across rows).  Bin NB of a
-  // row takes the increments of keys outside the
-  // interval, so that every key can be counted without a branch.
+  // Bin-major layout, entry (bin, row) at bin * kHistStride + row.  The odd
+  // stride spreads a row's bins over the banks for the final copy, which reads
+  // 64 bins of one row at a time (one bank, 64 ways, with a stride of 64 rows:
+  // 8k cycles per workgroup); an LDS atomic takes 4.1 cycles whatever its
+  // banks.  Bin NB of a row takes the increments of keys outside the interval,
+  // so that every key can be counted without a branch.
+  constexpr int kHistStride = kRowsWG + 1;
   constexpr int NB = kBins;
   constexpr int HS = NB + 1;  // bins per row including the spare one
   // The level-0 topP pass also sums each bin's softmax mass (terms exp2((s -
@@ -389,18 +412,16 @@ void k_score_pass(SelParams p) {
   // the levels before (bounds in the row state), so no key's mass is computed
   // there.
   constexpr bool MH = MODE == MODE_HIST0 && TOPP;
-  constexpr bool MASS = MODE != MODE_HIST && TOPP;  // this pass computes key masses
-  __shared__ uint32_t s_hist[HIST && !MH ? kRowsWG * HS : 1];
-  __shared__ uint64_t s_hist64[MH ? kRowsWG * HS : 1];
+  constexpr bool COL = MODE == MODE_COLLECT;
+  __shared__ uint32_t s_hist[HIST && !MH ? kHistStride * HS : 1];
+  __shared__ uint64_t s_hist64[MH ? kHistStride * HS : 1];
   __shared__ double s_zred[4][kRowsWG];
   __shared__ double s_mred[4][kRowsWG];
   __shared__ uint32_t s_nred[4][kRowsWG];
   __shared__ int s_part[kRowsWG];
-  __shared__ int s_any;
   // COLLECT: candidates are staged per row in LDS (rank from an LDS counter)
   // and written out with one global atomic per row at the end; a row that
   // overflows its LDS slots appends the rest directly.
-  constexpr bool COL = MODE == MODE_COLLECT;
   constexpr int kStage = 96;  // LDS candidate slots per row
   constexpr int kStageStride = kStage + 1;  // odd in 8-byte units: rows start in different banks
   __shared__ uint64_t s_cand[COL ? kRowsWG * kStageStride : 1];
@@ -408,7 +429,7 @@ void k_score_pass(SelParams p) {
   __shared__ uint32_t s_clo[COL ? kRowsWG : 1];
   __shared__ uint32_t s_chi[COL ? kRowsWG : 1];
   __shared__ uint32_t s_cbase[COL ? kRowsWG : 1];
-  // per lane: its 16 scores, the 16-byte chunk q stored at q ^ ((lane / 4) % 4) so
+  // per lane: 16 scores, the 16-byte chunk q stored at q ^ ((lane / 4) % 4) so
   // that the 16 lanes of a 16-byte store or load phase use distinct banks
   __shared__ __align__(16) float s_acc[COL ? 4 * 64 * 16 : 1];
   __shared__ uint32_t s_max[MODE == MODE_MAX ? kRowsWG : 1];  // ordered keys of row maxima
@@ -431,20 +452,60 @@ void k_score_pass(SelParams p) {
   const int64_t row0 = bh * p.Np + i0;
 
   const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63, g = lane >> 5, ln = lane & 31;
-  if (tid == 0) s_any = 0;
-  __syncthreads();
-  if (tid < kRowsWG) {
-    int part = 0;
-    if (tid < nrows) {
-      const int ph = p.st[row0 + tid].phase;
-      part = (HIST || MODE == MODE_MAX) ? ph == PH_HIST
-             : (MODE == MODE_COLLECT)        ? ph == PH_COLLECT
-                                             : ph == PH_EMIT;
-      if (MODE == MODE_MAX) part = part && (p.st[row0 + tid].mins || p.st[row0 + tid].topp);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, g = lane >> 5, ln = lane & 31;
+  // What the loop starts from (the pooled queries, the first K block) is loaded
+  // together with this lane's row state where all rows take part: one wait, not
+  // one after the other (each ~2 us when it misses L2, against ~20 us of work per
+  // workgroup).  The later levels look at the state first: most of their
+  // workgroups may be idle.
+  constexpr bool kEager = MODE != MODE_HIST;
+  const int64_t row = row0 + (lane < nrows ? lane : 0);
+  u32x4 stw[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) stw[j] = reinterpret_cast<const u32x4*>(p.st + row)[j];
+  // B operands: pooled query of rows 32 rb2 + ln (head-dim slots 16s + 8g .. +7).
+  bf16x8 qf[2][DS];
+  // K of a 32-key block as the A operand (lane -> key block_key_of_row(ln),
+  // head-dim slots 16s + 8g .. +7), from the operand-order copy: one coalesced
+  // 1 KB load per head-dim step (block indices are clamped, so loads past the
+  // end are safe).
+  const u32x4* const kbase = p.kop + (static_cast<int64_t>(b) * p.Hkv + hk) * p.nkb * (DS * 64) + lane;
+  auto kstep = [&](int blk, int s2) __attribute__((always_inline)) {
+    return kbase[(static_cast<int64_t>(min(key0 / 32 + blk, p.nkb - 1)) * DS + s2) * 64];
+  };
+  u32x4 ka[DS];
+  auto first_loads = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int rb2 = 0; rb2 < 2; ++rb2) {
+      const int rl = rb2 * 32 + ln;
+      const u32x4* src = reinterpret_cast<const u32x4*>(p.qp + (row0 + (rl < nrows ? rl : 0)) * D);
+#pragma unroll
+      for (int s2 = 0; s2 < DS; ++s2) {
+        const u32x4 t = rl < nrows ? src[2 * s2 + g] : u32x4{0, 0, 0, 0};
+        qf[rb2][s2] = __builtin_bit_cast(bf16x8, t);
+      }
     }
-    s_part[tid] = part;
-    if (part) atomicOr(&s_any, 1);
+#pragma unroll
+    for (int s2 = 0; s2 < DS; ++s2) ka[s2] = kstep(wave, s2);
+  };
+  if (kEager) first_loads();
+
+  // This lane's row; every wave holds all 64.
+  const int phase = static_cast<int>(stw[0][0]);
+  const bool row_topp = stw[0][1] != 0u;
+  bool part = lane < nrows &&
+              (HIST || MODE == MODE_MAX ? phase == PH_HIST
+               : COL                    ? phase == PH_COLLECT
+                                        : phase == PH_EMIT);
+  if (MODE == MODE_MAX) part = part && (row_topp || stw[0][2] != 0u);
+  if (!__any(part)) return;  // passes late in the refinement find most workgroups idle
+  if (!kEager) first_loads();
+  if (HIST) {
+    for (int t = tid; t < kHistStride * HS; t += kThreads) {
+      if (MH) s_hist64[t] = 0ull;
+      else s_hist[t] = 0u;
+    }
   }
   if (COL && tid < kRowsWG) {
     s_ccnt[tid] = 0u;
@@ -452,226 +513,269 @@ void k_score_pass(SelParams p) {
     s_chi[tid] = 0u;
   }
   if (MODE == MODE_MAX && tid < kRowsWG) s_max[tid] = 0u;  // below every ordered key
+  if (wave == 0) s_part[lane] = part;
   __syncthreads();
-  if (!s_any) return;  // passes late in the refinement find most workgroups idle
-  if (HIST) {
-    for (int t = tid; t < kRowsWG * HS; t += kThreads) {
-      if (MH) s_hist64[t] = 0ull;
-      else s_hist[t] = 0u;
-    }
-    __syncthreads();
-  }
-
-  // This lane's two rows (rl = 32 * rb2 + ln): pooled query as the B operand
-  // (head-dim slots 16s + 8g .. +7) and the row's interval in registers.
-  bf16x8 qf[2][DS];
-  bool part[2];
-  int Lr[2];
-  float slo[2], shi[2], bmul[2], badd[2], ts[2], smax[2];
-  bool tiep[2], tiei[2];
-  double ref[2];  // < 0: no masses needed
-#pragma unroll
-  for (int rb2 = 0; rb2 < 2; ++rb2) {
-    const int rl = rb2 * 32 + ln;
-    part[rb2] = rl < nrows && s_part[rl];
-    const int64_t row = row0 + (rl < nrows ? rl : 0);
-    const RowState& s = p.st[row];
-    Lr[rb2] = s.L;
-    slo[rb2] = s.s_lo;
-    shi[rb2] = s.s_hi;
-    bmul[rb2] = s.binv;
-    badd[rb2] = s.badd;
-    smax[rb2] = s.smax;
-    ts[rb2] = s.tstar;
-    tiep[rb2] = s.tie_partial;
-    tiei[rb2] = s.tie_interval;
-    ref[rb2] = (TOPP && s.topp) ? s.ref : -1.0;
-    const u32x4* src = reinterpret_cast<const u32x4*>(p.qp + row * D);
-#pragma unroll
-    for (int s2 = 0; s2 < DS; ++s2) {
-      const u32x4 t = rl < nrows ? src[2 * s2 + g] : u32x4{0, 0, 0, 0};
-      qf[rb2][s2] = __builtin_bit_cast(bf16x8, t);
-    }
-  }
+  const bool tiep = stw[2][2] != 0u;  // of row `lane`
+  // State of rows ln and 32 + ln.
+  auto both = [&](uint32_t x, uint32_t (&y)[2]) __attribute__((always_inline)) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    y[0] = r[0];
+    y[1] = r[1];
+  };
+  auto bothf = [&](uint32_t x, float (&y)[2]) __attribute__((always_inline)) {
+    uint32_t u[2];
+    both(x, u);
+    y[0] = __uint_as_float(u[0]);
+    y[1] = __uint_as_float(u[1]);
+  };
+  uint32_t Lr[2], tiei[2], mass[2];
+  float slo[2], shi[2], bmul[2], badd[2], smax[2], ts[2];
+  both(part ? stw[0][3] : 0u, Lr);
+  both(TOPP && row_topp && part ? 1u : 0u, mass);  // this row's masses are wanted
+  bothf(stw[1][0], slo);
+  bothf(stw[1][1], shi);
+  bothf(stw[1][2], bmul);
+  bothf(stw[1][3], badd);
+  bothf(stw[2][0], smax);
+  bothf(stw[2][1], ts);
+  both(stw[2][3], tiei);
+  uint32_t* const bsel = p.bsel + row * p.W;
+  uint32_t* const btie = p.btie + row * p.W;
 
   double zacc[2] = {0.0, 0.0}, macc[2] = {0.0, 0.0};
   const float tl2 = p.tau * 1.4426950408889634f;  // raw score -> log2 units
-  uint32_t nacc[2] = {0u, 0u};
+  uint32_t nacc[2] = {0u, 0u};  // COLLECT: nacc[0], of row `lane`
+  float fmx[2] = {kNegInf, kNegInf};
 
   const int nblk = (key1 - key0 + 31) / 32;
-  // K of a 32-key block as the A operand (lane -> key ln, head-dim slots
-  // 16s + 8g .. +7), from the operand-order copy: one coalesced 1 KB load per
-  // head-dim step.  The next block of this wave is loaded while the current
-  // one is processed (block indices are clamped, so loads past the end are safe).
-  auto kload = [&](u32x4 (&dst)[DS], int blk) __attribute__((always_inline)) {
-    const int kbi = min(key0 / 32 + blk, p.nkb - 1);
-    const u32x4* ksrc =
-        p.kop + ((static_cast<int64_t>(b) * p.Hkv + hk) * p.nkb + kbi) * (DS * 64) + lane;
-#pragma unroll
-    for (int s2 = 0; s2 < DS; ++s2) dst[s2] = ksrc[s2 * 64];
+  // Blocks whose keys are all eligible for every row of the tile.
+  const int Lfirst = eligible(i0, p.P, p.N, p.causal);
+  const int nfull = max(min(key1, Lfirst) - key0, 0) / 32;
+  auto mm = [&](f32x16& c0, f32x16& c1, const u32x4 k, int s2) __attribute__((always_inline)) {
+    c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k), qf[0][s2], c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k), qf[1][s2], c1, 0, 0, 0);
   };
-  auto kproc = [&](const u32x4 (&ka)[DS], int blk) __attribute__((always_inline)) {
-    const int kb = key0 + blk * 32;
+  // Words of 32 keys of row `lane` from the half-words of rows ln and 32 + ln
+  // (bit e: key 16 g + e).
+  auto word_of = [&](uint32_t w0, uint32_t w1) __attribute__((always_inline)) {
+    const auto r = __builtin_amdgcn_permlane32_swap(w0, w1, false, false);
+    return r[0] | (r[1] << 16);
+  };
+  // The work on one block (c[rb2]: keys 16 g .. of row 32 rb2 + ln).
+  auto work = [&](const f32x16& c0, const f32x16& c1, const int blk, const bool all_elig)
+      __attribute__((always_inline)) {
+    const int word = key0 / 32 + blk;
+    // Eligible keys of this lane's 16, per row; of row `lane`'s 32.
+    int n[2];
 #pragma unroll
-    for (int rb2 = 0; rb2 < 2; ++rb2) {
-      // Raw scores s = <q_p, k> of keys kl = 16 g + e of the block.
-      f32x16 acc = f32x16{};
+    for (int rb2 = 0; rb2 < 2; ++rb2) n[rb2] = static_cast<int>(Lr[rb2]) - (32 * word + 16 * g);
+    auto elig = [&](int rb2, int e) __attribute__((always_inline)) { return all_elig || e < n[rb2]; };
+    const int nr = static_cast<int>(g ? Lr[1] : Lr[0]) - 32 * word;
+    const uint32_t emask = all_elig || nr >= 32 ? 0xFFFFFFFFu : nr <= 0 ? 0u : (1u << nr) - 1u;
+    if (MODE == MODE_COLLECT) {
+      // Words (bit e: key e) of the keys at or above the interval (the kept set;
+      // the resolve step clears the candidates it rejects) and above it.  Their
+      // difference is the row's candidates.
+      uint32_t ge[2] = {0u, 0u}, gt[2] = {0u, 0u};
 #pragma unroll
-      for (int s2 = 0; s2 < DS; ++s2)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[s2]),
-                                                      qf[rb2][s2], acc, 0, 0, 0);
-      if (!part[rb2]) continue;
-      const int lim = Lr[rb2] - kb;  // keys kl < lim are eligible
-      // Whole block eligible for every row of the wave (all blocks but the
-      // last, unless causal): the per-key test folds away.
-      const bool full = !__any(lim < 32);
-      auto rowproc = [&](const bool all_elig) __attribute__((always_inline)) {
-        auto elig = [&](int kl) __attribute__((always_inline)) { return all_elig || kl < lim; };
-        if (MODE == MODE_MAX) {
-          float m = kNegInf;
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int kl = 16 * g + e;
-            if (elig(kl)) m = fmaxf(m, acc[e]);
-          }
-          m = fmaxf(m, __shfl_xor(m, 32));
-          if (g == 0) atomicMax(&s_max[rb2 * 32 + ln], ord_key(m));
-          return;
-        }
-        if (MODE == MODE_COLLECT) {
-          // Two words of this lane's 16 keys (bit e: key 16 g + e): at or above
-          // the interval (the kept set; the resolve step clears the candidates
-          // it rejects) and above it.  Their difference is the lane's candidates.
-          uint32_t wge = 0u, wgt = 0u;
-#pragma unroll
-          for (int e = 15; e >= 0; --e) {
-            uint64_t ge = lanes_ge(acc[e], slo[rb2]), gt = lanes_gt(acc[e], shi[rb2]);
-            if (!all_elig) {
-              const uint64_t ok = lanes_lt(16 * g + e, lim);
-              ge &= ok;
-              gt &= ok;
-            }
-            wge = shift_in(wge, ge);
-            wgt = shift_in(wgt, gt);
-            if (TOPP && ref[rb2] >= 0.0 && elig(16 * g + e) && acc[e] > shi[rb2])
-              macc[rb2] += static_cast<double>(__builtin_amdgcn_exp2f((acc[e] - smax[rb2]) * tl2));
-          }
-          nacc[rb2] += static_cast<uint32_t>(__builtin_popcount(wgt));
-          const uint32_t ins = wge & ~wgt;
-          const uint32_t wl = wge << (16 * g);
-          const uint32_t w = wl | __shfl_xor(wl, 32);
-          if (g == 0) p.bsel[(row0 + rb2 * 32 + ln) * p.W + kb / 32] = w;
-          if (__any(ins != 0u)) {
-            // The lane's scores go through LDS so that a candidate's score can
-            // be read by its (per-lane) position.
-            float* sc = s_acc + (wave * 64 + lane) * 16;
-            const int csw = (lane >> 2) & 3;
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-              *reinterpret_cast<f32x4*>(sc + 4 * (q4 ^ csw)) =
-                  f32x4{acc[4 * q4], acc[4 * q4 + 1], acc[4 * q4 + 2], acc[4 * q4 + 3]};
-            if (ins) {
-              const int rl = rb2 * 32 + ln;
-              uint32_t rank = atomicAdd(&s_ccnt[rl], static_cast<uint32_t>(__builtin_popcount(ins)));
-              uint32_t lo_k = 0xFFFFFFFFu, hi_k = 0u;
-              for (uint32_t m = ins; m; m &= m - 1u) {
-                const int e = __builtin_ctz(m);
-                const uint32_t okey = ord_key(sc[4 * ((e >> 2) ^ csw) + (e & 3)]);
-                const uint64_t entry =
-                    (static_cast<uint64_t>(okey) << 32) | (~static_cast<uint32_t>(kb + 16 * g + e));
-                lo_k = min(lo_k, okey);
-                hi_k = max(hi_k, okey);
-                if (rank++ < kStage) {
-                  s_cand[rl * kStageStride + rank - 1] = entry;
-                } else {  // LDS slots of this row full: append directly
-                  const int64_t row = row0 + rl;
-                  const uint32_t pos = atomicAdd(&p.cand_n[row], 1u);
-                  if (pos < kCand) p.cand[row * kCand + pos] = entry;
-                }
-              }
-              atomicMin(&s_clo[rl], lo_k);
-              atomicMax(&s_chi[rl], hi_k);
-            }
-          }
-          return;
-        }
-        if (MODE == MODE_EMIT) {
-          uint32_t wsel = 0u, wtie = 0u;
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int kl = 16 * g + e;
-            const bool ok = elig(kl);
-            wsel |= (ok && acc[e] > ts[rb2]) ? 1u << kl : 0u;
-            const bool tie = tiei[rb2] ? (acc[e] >= slo[rb2] && acc[e] <= shi[rb2])
-                                       : acc[e] == ts[rb2];
-            wtie |= (ok && tie) ? 1u << kl : 0u;
-          }
-          wsel |= __shfl_xor(wsel, 32);
-          wtie |= __shfl_xor(wtie, 32);
-          if (!tiep[rb2]) wsel |= wtie;
-          if (g == 0) {
-            const int64_t row = row0 + rb2 * 32 + ln;
-            p.bsel[row * p.W + kb / 32] = wsel;
-            if (tiep[rb2]) p.btie[row * p.W + kb / 32] = wtie;
-          }
-          return;
-        }
-        const int rl = rb2 * 32 + ln;
+      for (int e = 15; e >= 0; --e) {
+        ge[0] = shift_in(ge[0], lanes_ge(c0[e], slo[0]));
+        gt[0] = shift_in(gt[0], lanes_gt(c0[e], shi[0]));
+        ge[1] = shift_in(ge[1], lanes_ge(c1[e], slo[1]));
+        gt[1] = shift_in(gt[1], lanes_gt(c1[e], shi[1]));
+      }
+      const uint32_t wge = word_of(ge[0], ge[1]) & emask, wgt = word_of(gt[0], gt[1]) & emask;
+      if (TOPP) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int kl = 16 * g + e;
-          const float sc = acc[e];
-          const bool ok = elig(kl);
-          bool above = false, inside = ok;
-          if (MODE != MODE_HIST0) {  // level 0: the interval is everything
-            above = ok && sc > shi[rb2];
-            inside = ok && !above && sc >= slo[rb2];
-            nacc[rb2] += above ? 1u : 0u;
-          }
-          // topP: the key's softmax term relative to the row maximum, exp(tau
-          // s - ref) with ref = tau * max (terms below 2^-126, a share of the
-          // mass far below any tolerance, may flush to 0)
-          const float mt = MASS ? __builtin_amdgcn_exp2f((sc - smax[rb2]) * tl2) : 0.0f;
-          if (MASS && ref[rb2] >= 0.0 && ok) {
-            if (MODE == MODE_HIST0) zacc[rb2] += static_cast<double>(mt);
-            if (above) macc[rb2] += static_cast<double>(mt);
-          }
-          if (HIST) {
-            const int bn = inside ? bin_of(sc, bmul[rb2], badd[rb2], NB) : NB;
-            if (MH) {
-              const uint32_t mq = ref[rb2] >= 0.0
-                                      ? static_cast<uint32_t>(__builtin_fmaf(mt, 0x1p31f, 0.5f))
-                                      : 0u;
-              atomicAdd(reinterpret_cast<unsigned long long*>(&s_hist64[bn * kRowsWG + rl]),
-                        (1ull << kMassShift) | mq);
-            } else {
-              atomicAdd(&s_hist[bn * kRowsWG + rl], 1u);
-            }
-          }
+          const float m0 = __builtin_amdgcn_exp2f((c0[e] - smax[0]) * tl2);
+          const float m1 = __builtin_amdgcn_exp2f((c1[e] - smax[1]) * tl2);
+          macc[0] += static_cast<double>(c0[e] > shi[0] && elig(0, e) ? m0 : 0.0f);
+          macc[1] += static_cast<double>(c1[e] > shi[1] && elig(1, e) ? m1 : 0.0f);
         }
-      };
-      if (full) rowproc(true);
-      else rowproc(false);
+      }
+      nacc[0] += static_cast<uint32_t>(__builtin_popcount(wgt));
+      if (part && (all_elig || nr > 0)) bsel[word] = wge;
+      // Candidates of rows ln and 32 + ln among this lane's keys.  The lanes
+      // that hold one put their 16 scores of that row through LDS, so that a
+      // candidate's score can be read by its position.
+#pragma unroll
+      for (int rb2 = 0; rb2 < 2; ++rb2) {
+        uint32_t ins = ge[rb2] & ~gt[rb2];
+        if (!all_elig) ins &= n[rb2] >= 16 ? 0xFFFFu : n[rb2] <= 0 ? 0u : (1u << n[rb2]) - 1u;
+        if (!Lr[rb2]) ins = 0u;  // a row that does not take part
+        if (ins) {
+          const f32x16& c = rb2 ? c1 : c0;
+          float* sc = s_acc + (wave * 64 + lane) * 16;
+          const int csw = (lane >> 2) & 3;
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4)
+            *reinterpret_cast<f32x4*>(sc + 4 * (q4 ^ csw)) =
+                f32x4{c[4 * q4], c[4 * q4 + 1], c[4 * q4 + 2], c[4 * q4 + 3]};
+          const int rl = rb2 * 32 + ln;
+          uint32_t rank = atomicAdd(&s_ccnt[rl], static_cast<uint32_t>(__builtin_popcount(ins)));
+          uint32_t lo_k = 0xFFFFFFFFu, hi_k = 0u;
+          for (uint32_t m = ins; m; m &= m - 1u) {
+            const int e = __builtin_ctz(m);
+            const uint32_t okey = ord_key(sc[4 * ((e >> 2) ^ csw) + (e & 3)]);
+            const uint64_t entry = (static_cast<uint64_t>(okey) << 32) |
+                                   (~static_cast<uint32_t>(32 * word + 16 * g + e));
+            lo_k = min(lo_k, okey);
+            hi_k = max(hi_k, okey);
+            if (rank < kStage) {
+              s_cand[rl * kStageStride + rank] = entry;
+            } else {  // LDS slots of this row full: append directly
+              const uint32_t pos = atomicAdd(&p.cand_n[row0 + rl], 1u);
+              if (pos < kCand) p.cand[(row0 + rl) * kCand + pos] = entry;
+            }
+            ++rank;
+          }
+          atomicMin(&s_clo[rl], lo_k);
+          atomicMax(&s_chi[rl], hi_k);
+        }
+      }
+      return;
+    }
+    if (MODE == MODE_EMIT) {
+      uint32_t sel[2] = {0u, 0u}, tie[2] = {0u, 0u};
+#pragma unroll
+      for (int rb2 = 0; rb2 < 2; ++rb2)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const float sc = rb2 ? c1[e] : c0[e];
+          sel[rb2] |= sc > ts[rb2] ? 1u << e : 0u;
+          const bool t = tiei[rb2] ? (sc >= slo[rb2] && sc <= shi[rb2]) : sc == ts[rb2];
+          tie[rb2] |= t ? 1u << e : 0u;
+        }
+      uint32_t wsel = word_of(sel[0], sel[1]) & emask;
+      const uint32_t wtie = word_of(tie[0], tie[1]) & emask;
+      if (!tiep) wsel |= wtie;
+      if (part && (all_elig || nr > 0)) {
+        bsel[word] = wsel;
+        if (tiep) btie[word] = wtie;
+      }
+      return;
     }
   };
-  u32x4 k0[DS], k1[DS];
-  kload(k0, wave);
-  for (int blk = wave; blk < nblk; blk += 8) {
-    kload(k1, blk + 4);
-    kproc(k0, blk);
-    if (blk + 4 >= nblk) break;
-    kload(k0, blk + 8);
-    kproc(k1, blk + 4);
+  // The same for one half at a time (rows 32 rb2 + ln), histograms and maxima.
+  auto work_half = [&](const f32x16& c, const int rb2, const int blk, const bool all_elig)
+      __attribute__((always_inline)) {
+    const int n = static_cast<int>(Lr[rb2]) - (key0 + 32 * blk + 16 * g);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const bool ok = all_elig || e < n;
+      if (MODE == MODE_MAX) {
+        fmx[rb2] = ok ? fmaxf(fmx[rb2], c[e]) : fmx[rb2];
+        continue;
+      }
+      bool inside = ok;
+      if (MODE != MODE_HIST0) {  // level 0: the interval is everything
+        const bool above = ok && c[e] > shi[rb2];
+        inside = ok && !above && c[e] >= slo[rb2];
+        nacc[rb2] += above ? 1u : 0u;
+      }
+      const int bn = inside ? bin_of(c[e], bmul[rb2], badd[rb2], NB) : NB;
+      const int at = bn * kHistStride + 32 * rb2 + ln;
+      if (MH) {
+        // The key's softmax term relative to the row maximum, exp(tau s - ref)
+        // with ref = tau * max (terms below 2^-126, a share of the mass far
+        // below any tolerance, may flush to 0).
+        const float mt = __builtin_amdgcn_exp2f((c[e] - smax[rb2]) * tl2);
+        if (mass[rb2] && ok) zacc[rb2] += static_cast<double>(mt);
+        const uint32_t mq = mass[rb2] ? static_cast<uint32_t>(__builtin_fmaf(mt, 0x1p31f, 0.5f)) : 0u;
+        atomicAdd(reinterpret_cast<unsigned long long*>(&s_hist64[at]), (1ull << kMassShift) | mq);
+      } else {
+        atomicAdd(&s_hist[at], 1u);
+      }
+    }
+  };
+  // This wave takes blocks wave, wave + 4, ...
+  if constexpr (PIPE) {
+    // Scheduling of one pipelined step: each MFMA of the next block followed by
+    // its share of this block's vector instructions.
+    auto interleave = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < 2 * DS; ++j) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                          // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x002, 9 * 8 / DS, 0);   // VALU
+      }
+    };
+    // Each head-dim step's K is loaded again for the next block as soon as its
+    // MFMAs have read it.
+    f32x16 a0, a1;
+    auto scores = [&](f32x16& c0, f32x16& c1, int next) __attribute__((always_inline)) {
+      c0 = f32x16{};
+      c1 = f32x16{};
+#pragma unroll
+      for (int s2 = 0; s2 < DS; ++s2) {
+        mm(c0, c1, ka[s2], s2);
+        ka[s2] = kstep(next, s2);
+      }
+    };
+    // The work on block `at` (scores c) beside the scores of the next one (n).
+    auto step = [&](const f32x16& c0, const f32x16& c1, f32x16& n0, f32x16& n1, int at)
+        __attribute__((always_inline)) {
+      scores(n0, n1, at + 8);
+      work(c0, c1, at, true);
+      interleave();
+    };
+    int blk = wave;
+    scores(a0, a1, wave + 4);
+    // (topP's COLLECT also sums masses: pipelined it spills, 3.25 ms at the 131k
+    // VLM layer against 3.04 one block at a time.)
+    if constexpr (!(COL && TOPP)) {
+      f32x16 b0, b1;
+      for (; blk + 4 < nfull; blk += 8) {
+        step(a0, a1, b0, b1, blk);
+        step(b0, b1, a0, a1, blk + 4);
+      }
+    }
+    // The blocks left over (at most one whole one, then those with ineligible
+    // keys), one at a time.
+    for (; blk < nblk; blk += 4) {
+      if (blk < nfull) work(a0, a1, blk, true);
+      else work(a0, a1, blk, false);
+      if (blk + 4 < nblk) scores(a0, a1, blk + 8);
+    }
+  } else {
+    // Half by half, the next block's K loaded meanwhile.
+    u32x4 kb[DS];
+    auto kload = [&](u32x4 (&dst)[DS], int at) __attribute__((always_inline)) {
+#pragma unroll
+      for (int s2 = 0; s2 < DS; ++s2) dst[s2] = kstep(at, s2);
+    };
+    auto block = [&](const u32x4 (&k)[DS], int at) __attribute__((always_inline)) {
+#pragma unroll
+      for (int rb2 = 0; rb2 < 2; ++rb2) {
+        f32x16 c = f32x16{};
+#pragma unroll
+        for (int s2 = 0; s2 < DS; ++s2)
+          c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k[s2]), qf[rb2][s2], c,
+                                                      0, 0, 0);
+        if (at < nfull) work_half(c, rb2, at, true);
+        else work_half(c, rb2, at, false);
+      }
+    };
+    for (int blk = wave; blk < nblk; blk += 8) {
+      kload(kb, blk + 4);
+      block(ka, blk);
+      if (blk + 4 >= nblk) break;
+      kload(ka, blk + 8);
+      block(kb, blk + 4);
+    }
   }
   if (MODE == MODE_EMIT) return;
   if (MODE == MODE_MAX) {
+    atomicMax(&s_max[ln], ord_key(fmx[0]));
+    atomicMax(&s_max[32 + ln], ord_key(fmx[1]));
     __syncthreads();
     if (tid < nrows && s_part[tid]) atomicMax(&p.cand_lohi[2 * (row0 + tid) + 1], s_max[tid]);
     return;
   }
 
-  // Reduce per-row partials: lanes (ln, g = 0 / 1) of each wave, then the 4
-  // waves in a fixed order (deterministic sums).
+  // Per-row partials: the two half-waves, then the 4 waves in a fixed order
+  // (deterministic sums).
+  if (COL) s_nred[wave][lane] = nacc[0];
 #pragma unroll
   for (int rb2 = 0; rb2 < 2; ++rb2) {
     const double z = zacc[rb2] + __shfl_xor(zacc[rb2], 32);
@@ -680,18 +784,17 @@ void k_score_pass(SelParams p) {
     if (g == 0) {
       s_zred[wave][rb2 * 32 + ln] = z;
       s_mred[wave][rb2 * 32 + ln] = m;
-      s_nred[wave][rb2 * 32 + ln] = n;
+      if (!COL) s_nred[wave][rb2 * 32 + ln] = n;
     }
   }
   __syncthreads();
   if (COL) {  // staged candidates: one atomic per row, then the copy
     if (tid < nrows && s_part[tid]) {
-      const int64_t row = row0 + tid;
       const uint32_t c = min(s_ccnt[tid], static_cast<uint32_t>(kStage));
-      s_cbase[tid] = c ? atomicAdd(&p.cand_n[row], c) : 0u;
+      s_cbase[tid] = c ? atomicAdd(&p.cand_n[row0 + tid], c) : 0u;
       if (s_ccnt[tid]) {
-        atomicMin(&p.cand_lohi[2 * row], s_clo[tid]);
-        atomicMax(&p.cand_lohi[2 * row + 1], s_chi[tid]);
+        atomicMin(&p.cand_lohi[2 * (row0 + tid)], s_clo[tid]);
+        atomicMax(&p.cand_lohi[2 * (row0 + tid) + 1], s_chi[tid]);
       }
     }
     __syncthreads();
@@ -703,19 +806,19 @@ void k_score_pass(SelParams p) {
     }
   }
   if (tid < nrows && s_part[tid]) {
-    const int64_t row = row0 + tid;
+    const int64_t r = row0 + tid;
     const double z = ((s_zred[0][tid] + s_zred[1][tid]) + s_zred[2][tid]) + s_zred[3][tid];
     const double m = ((s_mred[0][tid] + s_mred[1][tid]) + s_mred[2][tid]) + s_mred[3][tid];
     const uint32_t n = s_nred[0][tid] + s_nred[1][tid] + s_nred[2][tid] + s_nred[3][tid];
-    p.n_above[row * p.nsplit + sp] = n;
-    p.m_above[row * p.nsplit + sp] = m;
-    if (MODE == MODE_HIST0) p.zpart[row * p.nsplit + sp] = z;
+    p.n_above[r * p.nsplit + sp] = n;
+    p.m_above[r * p.nsplit + sp] = m;
+    if (MODE == MODE_HIST0) p.zpart[r * p.nsplit + sp] = z;
   }
   if (HIST) {
     for (int t = tid; t < nrows * NB; t += kThreads) {
       const int rl = t / NB, bn = t % NB;
-      const uint64_t v = MH ? s_hist64[bn * kRowsWG + rl] : 0ull;
-      const uint32_t c = MH ? static_cast<uint32_t>(v >> kMassShift) : s_hist[bn * kRowsWG + rl];
+      const uint64_t v = MH ? s_hist64[bn * kHistStride + rl] : 0ull;
+      const uint32_t c = MH ? static_cast<uint32_t>(v >> kMassShift) : s_hist[bn * kHistStride + rl];
       if (c && s_part[rl]) {
         atomicAdd(&p.hist[(row0 + rl) * kBins + bn], c);
         const uint64_t m = v & ((1ull << kMassShift) - 1ull);
@@ -1188,106 +1291,102 @@ __global__ __launch_bounds__(256) void k_tiled_init(SelParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// Resolve after a HIST pass: one wave per row.
+// Resolve after a HIST pass: one wave per row, four rows per workgroup, every
+// step over the lanes (bins two per lane, splits one per lane, the float search
+// of `narrow` 64 probes at a time): with the sums, topP's walk over the bins and
+// the search on one lane it took 150 us at the 75k DiT layer and 440 at the
+// 131k VLM layer.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void k_resolve_hist(SelParams p, int level) {
+__global__ __launch_bounds__(256) void k_resolve_hist(SelParams p, int level) {
   if (level > 0 && p.nact[level] == 0u) return;
-  const int64_t r = blockIdx.x;
-  RowState& s = p.st[r];
-  if (s.phase != PH_HIST || s.level != level) return;
-  __shared__ uint32_t hs[kBins];
-  __shared__ double hm[kBins];
-  const int lane = threadIdx.x;
-  const int nb = kBins;
-  for (int t = lane; t < nb; t += 64) {
-    hs[t] = p.hist[r * kBins + t];
-    p.hist[r * kBins + t] = 0u;  // ready for the next level
-    if (s.topp) {
-      hm[t] = static_cast<double>(p.hmass[r * kBins + t]) * kMassUnit;
-      p.hmass[r * kBins + t] = 0ull;
-    }
+  const int64_t r = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (r >= p.rows) return;
+  RowState& st = p.st[r];
+  if (st.phase != PH_HIST || st.level != level) return;
+  RowState s = st;
+  const int lane = threadIdx.x & 63;
+  constexpr int nb = kBins;
+  static_assert(kBins == 2 * 64, "two bins per lane");
+  // Lane l holds bins nb - 1 - 2 l (hb[0]) and the one below it (hb[1]).
+  const int b1 = nb - 2 - 2 * lane;
+  int hb[2];
+  double hm[2] = {0.0, 0.0};
+  {
+    u32x2* h = reinterpret_cast<u32x2*>(p.hist + r * nb + b1);
+    const u32x2 w = *h;
+    *h = u32x2{0u, 0u};  // ready for the next level
+    hb[0] = static_cast<int>(w[1]);
+    hb[1] = static_cast<int>(w[0]);
   }
-  __syncthreads();
-  // Sum the per-split statistics in split order (every lane alike).
+  if (s.topp) {
+    uint64_t* m = p.hmass + r * nb + b1;
+    hm[0] = static_cast<double>(m[1]) * kMassUnit;
+    hm[1] = static_cast<double>(m[0]) * kMassUnit;
+    m[0] = m[1] = 0ull;
+  }
+  // The splits' statistics: keys above the interval (none at level 0), and at
+  // level 0 the total mass of topP rows.  (The mass above the interval of topP
+  // rows is carried in the row state.)
   const int i = static_cast<int>(r % p.Np);
   const int rb = i / kRowsWG;
   const int i_last = min(p.Np, (rb + 1) * kRowsWG) - 1;
   const int Ltile = eligible(i_last, p.P, p.N, p.causal);
   const int ns = (Ltile + p.split - 1) / p.split;
-  // (The mass above the interval of topP rows is carried in the row state.)
-  uint32_t nab = 0;
+  int nab = 0;
   double z = 0.0;
-  for (int q = 0; q < ns; ++q) {
-    nab += p.n_above[r * p.nsplit + q];
-    if (level == 0) z += p.zpart[r * p.nsplit + q];
-  }
-  // Count cut (topK, and minS rows over cap) across the wave: lane l holds
-  // bins nb - 1 - 2 l - j (j < 2, descending), and the scan counts the keys in
-  // every bin from the top through them.  The cut bin is the highest bin whose
-  // count from the top reaches the target rank (never an empty bin: the bin
-  // above it fell short); `cut_above` counts the keys in the bins above it.
-  static_assert(kBins == 2 * 64, "two bins per lane");
-  constexpr int per = 2;
-  int hb[2];
+  if (level > 0 || s.mins)
+    for (int q = lane; q < ns; q += 64) nab += static_cast<int>(p.n_above[r * p.nsplit + q]);
+  if (level == 0 && s.topp)
+    for (int q = lane; q < ns; q += 64) z += p.zpart[r * p.nsplit + q];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) hb[j] = static_cast<int>(hs[nb - 1 - per * lane - j]);
+  for (int o = 32; o > 0; o >>= 1) {
+    nab += __shfl_xor(nab, o);
+    z += __shfl_xor(z, o);
+  }
   const int lsum = hb[0] + hb[1];
   const int incl = wave_incl_scan(lsum);
   const int total_in = __builtin_amdgcn_readlane(incl, 63);
-  int cut_bin = -1, cut_above = 0;
-  if (!s.topp) {
-    const bool over_cap = s.mins && static_cast<uint32_t>(total_in) + nab >
-                                        static_cast<uint32_t>(p.cap);
-    const int kt = over_cap ? static_cast<int>(p.cap) : s.k_target;
-    const int want = max(kt - static_cast<int>(nab), 1);
-    const uint64_t hit = __ballot(incl >= want);
-    if (hit != 0ull) {
-      const int src = __builtin_ctzll(hit);  // lowest lane: the highest bins
-      int c = incl - lsum, jb = 1;  // in lane src: the first j whose count reaches `want`
-      if (c + hb[0] >= want) jb = 0;
-      else c += hb[0];
-      cut_bin = __builtin_amdgcn_readlane(nb - 1 - per * lane - jb, src);
-      cut_above = __builtin_amdgcn_readlane(c, src);
-    } else {  // cannot happen unless the counts disagree: the lowest non-empty bin
-      const uint64_t ne = __ballot(lsum > 0);
-      if (ne != 0ull) {
-        const int src = 63 - __builtin_clzll(ne);  // highest lane: the lowest bins
-        const int jb = hb[1] != 0 ? 1 : 0;
-        cut_bin = __builtin_amdgcn_readlane(nb - 1 - per * lane - jb, src);
-        const int h_low = jb == 0 ? hb[0] : hb[1];
-        cut_above = total_in - __builtin_amdgcn_readlane(h_low, src);
-      }
-    }
-  }
-  if (lane != 0) return;
+  const uint64_t nonempty = __ballot(lsum > 0);
   if (level == 0 && s.topp) {
     s.Z = z;
     s.pZ = row_param(p, r) * z;
   }
   const float lo = s.blo, inv = s.binv, add = s.badd;
   const float top = static_cast<float>(s.ref / static_cast<double>(p.tau));  // raw score bound
-  int ba = -1, bb = -1;
-  uint32_t above_bins = 0;  // keys in bins above bb (inside the interval)
   if (s.mins) {  // level 0 of a minS row: the histogram counts the keys it keeps
     s.mins = 0;
-    const uint32_t tot = static_cast<uint32_t>(total_in) + nab;
-    if (tot <= static_cast<uint32_t>(p.cap)) {
-      s.tstar = s.s_lo;  // the emit pass keeps s > t* and, all ties kept, s == t*
-      s.tie_partial = 0;
-      s.tie_interval = 0;
-      s.k_eq = 0;
-      s.count = static_cast<int>(tot);
-      s.level = level + 1;
-      s.phase = PH_EMIT;
-      atomicAdd(&p.nact[kEmitSlot], 1u);
+    const int64_t tot = static_cast<int64_t>(total_in) + nab;
+    if (tot <= p.cap) {
+      if (lane == 0) {
+        st.mins = 0;
+        st.tstar = s.s_lo;  // the emit pass keeps s > t* and, all ties kept, s == t*
+        st.tie_partial = 0;
+        st.tie_interval = 0;
+        st.k_eq = 0;
+        st.count = static_cast<int>(tot);
+        st.level = level + 1;
+        st.phase = PH_EMIT;
+        atomicAdd(&p.nact[kEmitSlot], 1u);
+      }
       return;
     }
     s.k_target = static_cast<int>(p.cap);  // more than cap: keep the cap best
     s.clamped = 1;
   }
+  int ba = -1, bb = -1;
   if (!s.topp) {
-    ba = bb = cut_bin;  // from the wave scan above (target: k_target, or cap for minS)
-    above_bins = static_cast<uint32_t>(cut_above);
+    // The highest bin whose count from the top reaches the target rank (never
+    // an empty bin: the bin above it fell short).
+    const int want = max(s.k_target - nab, 1);
+    const uint64_t hit = __ballot(incl >= want);
+    if (hit != 0ull) {
+      const int src = __builtin_ctzll(hit);  // lowest lane: the highest bins
+      const int jb = incl - lsum + hb[0] >= want ? 0 : 1;
+      ba = bb = __builtin_amdgcn_readlane(nb - 1 - 2 * lane - jb, src);
+    } else if (nonempty != 0ull) {  // cannot happen unless the counts disagree: the lowest bin
+      const int src = 63 - __builtin_clzll(nonempty);
+      ba = bb = __builtin_amdgcn_readlane(hb[1] != 0 ? b1 : b1 + 1, src);
+    }
   } else {
     // Mass bounds per bin: from its score range (count times the mass at
     // each edge) and, at level 0, from its mass sum -- the terms exp(tau s -
@@ -1304,53 +1403,68 @@ __global__ __launch_bounds__(64) void k_resolve_hist(SelParams p, int level) {
     const float k1 = p.tau * 1.4426950408889634f;
     const float w = 1.0f / inv;
     const float slop = fabsf(w) * 1e-3f + fabsf(lo) * 1e-6f;
-    double before_lo = 0.0, before_hi = 0.0, cut_lo = 0.0, cut_hi = 0.0;
-    int top_nonempty = -1;
-    for (int bn = nb - 1; bn >= 0; --bn) {
-      if (hs[bn] == 0) continue;
-      if (top_nonempty < 0) top_nonempty = bn;
+    double mlo[2] = {0.0, 0.0}, mhi[2] = {0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int bn = nb - 1 - 2 * lane - j;
+      if (hb[j] == 0) continue;
       float e_lo = lo + static_cast<float>(bn) * w - slop;
       float e_hi = lo + static_cast<float>(bn + 1) * w + slop;
       if (level == 0 && bn == 0) e_lo = -FLT_MAX;
       if (level == 0 && bn == nb - 1) e_hi = top;
-      double mlo = hs[bn] * mass_term(e_lo, p.tau, s.ref);
-      double mhi = hs[bn] * mass_term(fminf(e_hi, top), p.tau, s.ref);
+      mlo[j] = hb[j] * mass_term(e_lo, p.tau, s.ref);
+      mhi[j] = hb[j] * mass_term(fminf(e_hi, top), p.tau, s.ref);
       if (level == 0) {
-        const double grid = static_cast<double>(hs[bn]) * 0x1p-32;
+        const double grid = static_cast<double>(hb[j]) * 0x1p-32;
         const double xmax = (static_cast<double>(s.smax) - static_cast<double>(e_lo)) * k1;
         const double eps = fmin(1.0, (2.0 + xmax) * 0x1p-22);
-        mlo = fmax(mlo, hm[bn] * (1.0 - eps) - grid);
-        mhi = fmin(mhi, hm[bn] * (1.0 + eps) + grid);
+        mlo[j] = fmax(mlo[j], hm[j] * (1.0 - eps) - grid);
+        mhi[j] = fmin(mhi[j], hm[j] * (1.0 + eps) + grid);
       }
-      if (bb < 0) {
-        if (before_hi + mhi >= T_lo) {  // the mass through bn may reach T
-          bb = ba = bn;
-          cut_lo = before_lo;
-          cut_hi = before_hi;
-        }
-      } else if (before_lo < Trel) {
-        ba = bn;  // the mass above bn may still fall short of T - slack
-      } else {
-        break;
+    }
+    // Bounds of the mass through each bin from the top, and above it.
+    const double in_lo = wave_scan(mlo[0] + mlo[1]), in_hi = wave_scan(mhi[0] + mhi[1]);
+    const double above_lo[2] = {in_lo - mlo[0] - mlo[1], in_lo - mlo[1]};
+    const double above_hi[2] = {in_hi - mhi[0] - mhi[1], in_hi - mhi[1]};
+    // bb: the highest bin with keys through which the mass may reach T.
+    const bool r0 = hb[0] > 0 && above_hi[1] >= T_lo, r1 = hb[1] > 0 && in_hi >= T_lo;
+    const uint64_t reach = __ballot(r0 || r1);
+    if (reach != 0ull) {
+      const int src = __builtin_ctzll(reach);
+      const int jb = r0 ? 0 : 1;
+      bb = __builtin_amdgcn_readlane(nb - 1 - 2 * lane - jb, src);
+      // the bins above bb join the mass above the interval
+      s.mab_lo += __shfl(above_lo[0], src);
+      s.mab_hi += __shfl(above_hi[0], src);
+      if (__builtin_amdgcn_readlane(jb, src) == 1) {
+        s.mab_lo += __shfl(mlo[0], src);
+        s.mab_hi += __shfl(mhi[0], src);
       }
-      before_lo += mlo;
-      before_hi += mhi;
-      if (bb >= 0 && before_lo >= Trel) break;
+      // ba: the lowest bin with keys at or below bb above which the mass may
+      // still fall short of T - slack.
+      ba = bb;
+      const bool f0 = hb[0] > 0 && above_lo[0] < Trel, f1 = hb[1] > 0 && above_lo[1] < Trel;
+      const uint64_t shrt = __ballot(f0 || f1);
+      if (shrt != 0ull) {
+        const int low = 63 - __builtin_clzll(shrt);  // highest lane: the lowest bins
+        ba = min(ba, __builtin_amdgcn_readlane(f1 ? b1 : b1 + 1, low));
+      }
+    } else {  // T <= 0 or rounding: the cut is at the top of the interval
+      bb = ba = 0;
+      if (nonempty != 0ull)
+        bb = ba = __builtin_amdgcn_readlane(hb[0] != 0 ? b1 + 1 : b1, __builtin_ctzll(nonempty));
     }
-    if (bb < 0) {  // T <= 0 or rounding: the cut is at the top of the interval
-      bb = ba = top_nonempty >= 0 ? top_nonempty : 0;
-    }
-    s.mab_lo += cut_lo;  // the bins above bb join the mass above the interval
-    s.mab_hi += cut_hi;
   }
-  uint32_t inside = 0;
-  for (int bn = ba; bn <= bb; ++bn) inside += hs[bn];
-  (void)above_bins;
+  // Keys of the chosen bins.
+  int inside = (b1 + 1 >= ba && b1 + 1 <= bb ? hb[0] : 0) + (b1 >= ba && b1 <= bb ? hb[1] : 0);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) inside += __shfl_xor(inside, o);
   // New interval: the chosen bins of this level, as exact float bounds.
   narrow(s.s_lo, s.s_hi, inv, add, ba, bb, nb);
+  if (lane != 0) return;
   const int nl = level + 1;
   s.level = nl;
-  if (inside <= static_cast<uint32_t>(kCand) || nl >= kLevels) {
+  if (inside <= kCand || nl >= kLevels) {
     s.phase = PH_COLLECT;
   } else {
     atomicAdd(&p.nact[nl], 1u);
@@ -1361,6 +1475,7 @@ __global__ __launch_bounds__(64) void k_resolve_hist(SelParams p, int level) {
     const float nhi = bb == nb - 1 ? fminf(s.s_hi, top) : lo + static_cast<float>(bb + 1) / inv;
     set_bins(s, nlo, static_cast<float>(nb) / fmaxf(nhi - nlo, FLT_MIN));
   }
+  st = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -1436,6 +1551,7 @@ __global__ __launch_bounds__(256) void k_resolve_cand(SelParams p) {
         s.k_target = static_cast<int>(p.cap);
         s.clamped = 1;
         s.phase = PH_IDLE;
+        atomicAdd(&p.nact[kRedoSlot], 1u);
         res[0] = -1;
       } else {
         n_sel = static_cast<int>(p.cap - nab);
@@ -1766,6 +1882,7 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
   hipError_t e = launch_pool(a.q, P, const_cast<uint16_t*>(p.qp), Hq * Np * D, Np * D, D, stream);
   if (e != hipSuccess) return e;
   const dim3 rgrid(static_cast<unsigned>(rows));
+  const dim3 qgrid(static_cast<unsigned>((rows + 3) / 4));
   const dim3 igrid(static_cast<unsigned>((rows + 255) / 256));
   {  // K in operand order, and the largest key norm per head
     hipLaunchKernelGGL(k_kmax_init, dim3(static_cast<unsigned>((B * Hkv + 255) / 256)), dim3(256),
@@ -1857,12 +1974,14 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
     for (int lv = 0; lv < kLevels; ++lv) {
       // Level 0 bins every key, except for minS rows, which count [threshold, max].
       SelParams pl = p;
-      pl.gate = lv > 0 ? lv : -1;
+      pl.gate = lv > 0 ? lv : round > 0 ? kRedoSlot : -1;
       if (lv == 0 && !p.mode_mins) score_pass<MODE_HIST0>(D, p.mode_topp != 0, pgrid, pl, stream);
       else score_pass<MODE_HIST>(D, p.mode_topp != 0, pgrid, pl, stream);
-      hipLaunchKernelGGL(k_resolve_hist, rgrid, dim3(64), 0, stream, p, lv);
+      hipLaunchKernelGGL(k_resolve_hist, qgrid, dim3(256), 0, stream, p, lv);
     }
-    score_pass<MODE_COLLECT>(D, p.mode_topp != 0, pgrid, p, stream);
+    SelParams pc = p;
+    pc.gate = round > 0 ? kRedoSlot : -1;
+    score_pass<MODE_COLLECT>(D, p.mode_topp != 0, pgrid, pc, stream);
     hipLaunchKernelGGL(k_resolve_cand, rgrid, dim3(256), 0, stream, p);
   }
   {

@@ -53,6 +53,18 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
   return x;
 }
 
+// Inclusive prefix sums over the wave of a 64-bit count or an fp64 mass.
+template <typename T>
+__device__ __forceinline__ T wave_scan(T x) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const T y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  return x;
+}
+
 // Orders this wave's LDS accesses on either side (a one-wave workgroup needs
 // no barrier).  Unlike __syncthreads() it does not wait for the wave's
 // global loads and stores: the prefetched bitmask words stay in flight and

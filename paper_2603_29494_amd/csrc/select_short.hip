@@ -152,18 +152,6 @@ __global__ __launch_bounds__(256) void k_short_scores(ShortParams p) {
   }
 }
 
-// Inclusive prefix sums over the wave of a 64-bit count or an fp64 mass.
-template <typename T>
-__device__ __forceinline__ T wave_scan(T x) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const T y = __shfl_up(x, o);
-    if (lane >= o) x += y;
-  }
-  return x;
-}
-
 // ---------------------------------------------------------------------------
 // The cut and the list of one row.  A lane holds 4 * E4 scores, wave w the keys
 // [w * E4 * 256, + E4 * 256) of the row (groups of 256 keys, 4 consecutive ones
