@@ -33,6 +33,12 @@ struct SparseAttnArgs {
 
 hipError_t launch_sparse_attn(const SparseAttnArgs& a, hipStream_t stream);
 
+// Packed sequences: a's tensors hold all rows, sequence s the rows
+// [cu[s], cu[s + 1]) of them; lists, counts and LSE lie sequence after sequence
+// (B = 1, no block order).
+hipError_t launch_sparse_attn_varlen(const SparseAttnArgs& a, const int64_t* cu, int32_t nseq,
+                                     hipStream_t stream);
+
 // Block order per (b, h) for the attention: blocks sorted by count (largest
 // first), then by a sampled mean key, then by index, within consecutive
 // segments of kOrderMaxBlocks blocks.  rows = B * Hq (fits the grid).

@@ -460,21 +460,11 @@ vecattn_status vecattn_sparse_attn_varlen(const void* q, const vecattn_tdesc* qd
                     cap, counts, block, causal, scale, seq_ptr(o, od, r0), &os);
     if (st != VECATTN_OK) return st;
   }
-  int64_t blocks = 0;
-  for (int32_t s = 0; s < nseq; ++s) {
-    const int64_t n = cu_seqlens[s + 1] - cu_seqlens[s];
-    if (n == 0) continue;
-    const int64_t r0 = cu_seqlens[s];
-    const vecattn_tdesc qs = seq_desc(qd, n), ks = seq_desc(kd, n), vs = seq_desc(vd, n),
-                        os = seq_desc(od, n);
-    st = vecattn_sparse_attn(seq_ptr(q, qd, r0), &qs, seq_ptr(k, kd, r0), &ks, seq_ptr(v, vd, r0),
-                             &vs, idx + blocks * qd->H * cap, cap, counts + blocks * qd->H, block,
-                             causal, scale, const_cast<void*>(seq_ptr(o, od, r0)), &os,
-                             lse ? lse + qd->H * r0 : nullptr, stream);
-    if (st != VECATTN_OK) return st;
-    blocks += num_blocks(n, block);
-  }
-  return VECATTN_OK;
+  vecattn::SparseAttnArgs a{to_tensor(q, qd), to_tensor(k, kd), to_tensor(v, vd),
+                            o, od->sB, od->sH, od->sN, lse, idx, counts, cap, block,
+                            (causal & kCausal) ? 1 : 0, scale, nullptr};
+  hipError_t e = vecattn::launch_sparse_attn_varlen(a, cu_seqlens, nseq, static_cast<hipStream_t>(stream));
+  return e == hipSuccess ? VECATTN_OK : VECATTN_ERR_DEVICE;
 }
 
 vecattn_status vecattn_plan_filter_ratios(int32_t heads, int32_t n_cand, const double* sparsity,

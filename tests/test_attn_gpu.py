@@ -331,3 +331,39 @@ def test_references_that_move_after_the_weights(gpu, N, D, P, causal, step):
     err = np.abs(got - o_ref)
     assert err.max() <= ATOL_MAX and err.mean() <= ATOL_MEAN, (err.max(), err.mean())
     assert np.abs(lse.cpu().numpy().astype(np.float64) - lse_ref).max() <= 3e-4
+
+
+@pytest.mark.parametrize("D,P,causal", [(128, 64, True), (64, 128, True), (128, 48, False), (64, 64, False)])
+def test_packed_sequences_match_separate_calls(gpu, D, P, causal):
+    """More sequences than one launch takes (32), empty ones and ragged lengths among them, K and
+    V rows of different strides: each sequence's O and LSE against a call on its rows alone
+    (causal: the same bits; else bf16 outputs within one rounding, LSE within fp32 sums)."""
+    r = np.random.Generator(np.random.PCG64(D + P))
+    lens = [1, 0, 700, 65, 64, 2] + [int(x) for x in r.integers(0, 400, 34)]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    Hq, Hkv, total = 6, 2, int(cu[-1])
+    q, k, v = (dev(synth.random_bits(s, (1, h, total, D))) for s, h in ((1, Hq), (2, Hkv), (3, Hkv)))
+    wide = torch.zeros(1, Hkv, total, D + 8, dtype=torch.bfloat16, device="cuda")
+    wide[..., :D] = v
+    v = wide[..., :D]
+    cap = max(va.max_count(n, P, causal, "topk", 0.4) for n in lens if n)
+    idx, cnt = va.select_varlen(q, k, cu, P, "topk", 0.4, causal, cap=cap)
+    out, lse = va.sparse_attn_varlen(q, k, v, cu, idx, cnt, cap, P, causal, return_lse=True)
+    nb, first, _ = va.varlen_blocks(cu, P)
+    for s, n in enumerate(lens):
+        if n == 0:
+            continue
+        a, z = int(cu[s]), int(cu[s + 1])
+        i_s = idx[first[s] * Hq * cap:(first[s] + nb[s]) * Hq * cap].view(1, Hq, nb[s], cap)
+        c_s = cnt[first[s] * Hq:(first[s] + nb[s]) * Hq].view(1, Hq, nb[s])
+        o1, l1 = va.sparse_attn(q[:, :, a:z], k[:, :, a:z], v[:, :, a:z], i_s, c_s, P, causal,
+                                return_lse=True)
+        o, l = out[:, :, a:z], lse[Hq * a:Hq * z].view(1, Hq, n)
+        if causal:
+            assert torch.equal(o.reshape(-1).view(torch.int16), o1.reshape(-1).view(torch.int16)), s
+            assert torch.equal(l, l1), s
+        else:
+            # the tiles' order differs: weights rounded to bf16 against other references (2^-9
+            # each, of outputs of order 1), then the output's own rounding
+            assert (o.float() - o1.float()).abs().max() <= 2e-2, s
+            assert (l - l1).abs().max() <= 1e-4, s
