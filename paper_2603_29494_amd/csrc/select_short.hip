@@ -168,13 +168,25 @@ __global__ __launch_bounds__(256) void k_short_scores(ShortParams p) {
 // topP: a bin carries its softmax mass (terms exp(tau (s - max)) <= 1, in units
 // of 2^-31) besides its count; the bin chosen by those sums is checked against
 // the fp64 sums of the terms above and inside it, and moved if they disagree.
-// Bound by instruction issue: ~15 per key in four passes (load, histogram,
-// collect, list).  A lane holds few keys (16, or 32 past 8192) and a row takes
+// Bound by instruction issue: ~20 per key in four passes (load, histogram,
+// collect, list); the passes handle the one group that may hold ineligible keys
+// apart (4096 tokens, 28 heads, topK: 39.8 -> 36.8 us).  A lane holds few keys (16, or 32 past 8192) and a row takes
 // more waves instead: with 64 keys per lane the unrolled passes spilled and
 // outgrew the instruction cache (288 us for 2700 rows of 12k tokens).
 // ---------------------------------------------------------------------------
+// Waves per SIMD the registers must leave room for.  A row of 8 waves puts two
+// on each SIMD, so 129 to 256 registers hold a CU to one row at a time: 28
+// heads, 12345 tokens, topK 15% 368 us with 136 registers, 276 with 128 (two
+// rows; 20 spilled), topP 575 us with 204, 520 with 128 (182 spilled); 7000
+// tokens 93 -> 82 (80 registers, three rows), topP 201 -> 147 (128, two).  The
+// four waves of a shorter row do without: 4096 tokens 36.5 us, 39.3 held to 64
+// registers, topP 51.7 and 53.5 held to 96.
 template <int W, int E4, bool TOPP>
-__global__ __launch_bounds__(64 * W) void k_short_select(ShortParams p) {
+constexpr int kSelectWaves = W < 8 ? 1 : E4 == 8 || TOPP ? 4 : 6;
+
+template <int W, int E4, bool TOPP>
+__global__ __launch_bounds__(64 * W)
+    __attribute__((amdgpu_waves_per_eu(kSelectWaves<W, E4, TOPP>))) void k_short_select(ShortParams p) {
   constexpr int kWaveKeys = 256 * E4;
   constexpr int kBinsS = W >= 8 ? 1024 : 256;  // bins of one histogram
   constexpr int kLaneBins = kBinsS / 64;
@@ -239,6 +251,8 @@ __global__ __launch_bounds__(64 * W) void k_short_select(ShortParams p) {
   // keys in its first `ng` groups.
   auto pos = [&](int j) __attribute__((always_inline)) { return wave * kWaveKeys + (j * 64 + lane) * 4; };
   const int ng = min(max((L - wave * kWaveKeys + 255) / 256, 0), E4);
+  // Every key of group j is eligible (uniform: all groups but one or none).
+  auto full = [&](int j) __attribute__((always_inline)) { return wave * kWaveKeys + (j + 1) * 256 <= L; };
   float f[4 * E4];
   float fmx = -FLT_MAX, fmn = FLT_MAX;
   {
@@ -249,14 +263,22 @@ __global__ __launch_bounds__(64 * W) void k_short_select(ShortParams p) {
       x[j] = pos(j) < L ? *reinterpret_cast<const f32x4*>(src + pos(j)) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int j = 0; j < E4; ++j) {
-      const bool full = wave * kWaveKeys + (j + 1) * 256 <= L;
+      if (full(j)) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const float y = fminf(fmaxf(x[j][c], -FLT_MAX), FLT_MAX);
-        const bool ok = full || pos(j) + c < L;
-        f[4 * j + c] = ok ? y : kNegInf;
-        fmx = fmaxf(fmx, f[4 * j + c]);
-        fmn = fminf(fmn, ok ? y : FLT_MAX);
+        for (int c = 0; c < 4; ++c) {
+          f[4 * j + c] = __builtin_amdgcn_fmed3f(x[j][c], -FLT_MAX, FLT_MAX);  // NaN: the lower bound
+          fmx = fmaxf(fmx, f[4 * j + c]);
+          fmn = fminf(fmn, f[4 * j + c]);
+        }
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float y = fminf(fmaxf(x[j][c], -FLT_MAX), FLT_MAX);
+          const bool ok = pos(j) + c < L;
+          f[4 * j + c] = ok ? y : kNegInf;
+          fmx = fmaxf(fmx, f[4 * j + c]);
+          fmn = fminf(fmn, ok ? y : FLT_MAX);
+        }
       }
     }
   }
@@ -317,8 +339,9 @@ __global__ __launch_bounds__(64 * W) void k_short_select(ShortParams p) {
     for (int level = 0; flo != fhi; ++level) {
       // First histogram: bin = floor(score * mul + add), clamped.  topP: the
       // mass lies within kTopPRange nats of the maximum; keys below that share
-      // bin 0.  A range too small or large for finite factors bins nothing
-      // (mul = 0) and leaves the work to the next histogram.
+      // bin 0.  A range too small or large for finite factors puts every key
+      // into bin 0 (mul = 0) and leaves the work to the next histogram; an
+      // ineligible key (-inf, or NaN after mul = 0) also falls there.
       const float base = by_mass ? fmaxf(flo, fhi - kTopPRange / p.tau) : flo;
       float mul = static_cast<float>(kBinsS) / (fhi - base);
       if (!(mul < 1e30f)) mul = 0.0f;
@@ -351,8 +374,7 @@ __global__ __launch_bounds__(64 * W) void k_short_select(ShortParams p) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {  // an ineligible key counts in bin 0 (taken off below)
               const float x = f[4 * j + c];
-              const float y = fmaxf(x, -FLT_MAX);
-              atomicAdd(&s_bins[mul == 0.0f ? 0 : bin0(y)], entry(x));
+              atomicAdd(&s_bins[bin0(x)], entry(x));
             }
           }
         } else {
@@ -434,8 +456,11 @@ __global__ __launch_bounds__(64 * W) void k_short_select(ShortParams p) {
             if (j >= ng) break;
             int bn[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-              bn[c] = f[4 * j + c] == kNegInf ? -1 : mul == 0.0f ? 0 : bin0(f[4 * j + c]);
+            for (int c = 0; c < 4; ++c) bn[c] = bin0(f[4 * j + c]);
+            if (!full(j)) {
+#pragma unroll
+              for (int c = 0; c < 4; ++c) bn[c] = f[4 * j + c] == kNegInf ? -1 : bn[c];
+            }
             if (bn[0] == cut || bn[1] == cut || bn[2] == cut || bn[3] == cut) {
 #pragma unroll
               for (int c = 0; c < 4; ++c)
@@ -561,55 +586,65 @@ __global__ __launch_bounds__(64 * W) void k_short_select(ShortParams p) {
   }
   if (clamped && tid == 0 && p.n_clamped) atomicAdd(p.n_clamped, 1);
 
-  // The list: the lane's kept keys, 4 consecutive ones per step, at their
-  // prefix places in LDS, then out in order, -1 behind.
-  uint32_t bits[E4];
-  int mine = 0;
-  touch();
+  // The list: a kept key's place is the number of kept keys before it, from
+  // the lane masks of its group's four compares (a prefix sum over the lanes'
+  // counts took three times the instructions), then out of LDS in order, -1
+  // behind.
+  int total = 0;
+  auto write_list = [&](auto kept) __attribute__((always_inline)) {
+    int n = 0;
+    touch();
 #pragma unroll
-  for (int j = 0; j < E4; ++j) {
-    uint32_t m = 0u;
-    if (j < ng) {
+    for (int j = 0; j < E4; ++j) {
+      if (j >= ng) break;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) m |= f[4 * j + c] >= tf ? 1u << c : 0u;
-      if (some) {
+      for (int c = 0; c < 4; ++c) n += __builtin_popcountll(__ballot(kept(j, c)));
+    }
+    int start = 0;
+    total = n;
+    if (W > 1) {
+      if (lane == 0) s_ru[turn][wave] = static_cast<uint32_t>(n);
+      __syncthreads();
+      total = 0;
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          if (f[4 * j + c] == tf && pos(j) + c > it) m &= ~(1u << c);
+      for (int w = 0; w < W; ++w) {
+        if (w < wave) start += static_cast<int>(s_ru[turn][w]);
+        total += static_cast<int>(s_ru[turn][w]);
       }
-      if (p.keep_diag) {  // the keys of the block's own rows
-        const int lo = i * p.P, hi = min(L, lo + p.P);
+      start = __builtin_amdgcn_readfirstlane(start);
+      total = __builtin_amdgcn_readfirstlane(total);
+    }
+    touch();
 #pragma unroll
-        for (int c = 0; c < 4; ++c) m |= pos(j) + c >= lo && pos(j) + c < hi ? 1u << c : 0u;
+    for (int j = 0; j < E4; ++j) {
+      if (j >= ng) break;
+      uint32_t at = static_cast<uint32_t>(start);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const uint64_t m = __ballot(kept(j, c));
+        at = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), at));
+        start += __builtin_popcountll(m);
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const bool k = kept(j, c);
+        if (k) s_list[at] = static_cast<uint16_t>(pos(j) + c);
+        at += k ? 1u : 0u;
       }
     }
-    bits[j] = m;
-    mine += __builtin_popcount(m);
+  };
+  if (!some && !p.keep_diag) {
+    write_list([&](int j, int c) __attribute__((always_inline)) { return f[4 * j + c] >= tf; });
+  } else {
+    // The keys of the block's own rows, where they are asked for.
+    const int dlo = p.keep_diag ? i * p.P : 0, dhi = p.keep_diag ? min(L, dlo + p.P) : 0;
+    write_list([&](int j, int c) __attribute__((always_inline)) {
+      const float x = f[4 * j + c];
+      const int key = pos(j) + c;
+      return (x > tf || (x == tf && (!some || key <= it))) || (key >= dlo && key < dhi);
+    });
   }
-  int start = 0, total = 0;
-  if (W > 1) {
-    const int n = wave_incl_scan(mine);
-    const uint32_t wtot = static_cast<uint32_t>(__builtin_amdgcn_readlane(n, 63));
-    if (lane == 0) s_ru[turn][wave] = wtot;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      if (w < wave) start += static_cast<int>(s_ru[turn][w]);
-      total += static_cast<int>(s_ru[turn][w]);
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < E4; ++j) {
-    if (j >= ng) break;
-    const int n = __builtin_popcount(bits[j]);
-    const int incl = wave_incl_scan(n);
-    int at = start + incl - n;
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      if ((bits[j] >> c) & 1u) s_list[at++] = static_cast<uint16_t>(pos(j) + c);
-    start += __builtin_amdgcn_readlane(incl, 63);
-  }
-  if (W == 1) total = start;
   sync();
   total = min(total, static_cast<int>(min<int64_t>(p.cap, p.N)));
   int32_t* out = p.idx + row * p.cap;
