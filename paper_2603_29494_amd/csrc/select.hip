@@ -316,9 +316,10 @@ __global__ __launch_bounds__(256) void k_sel_init(SelParams p, int round) {
     s.clamped = 0;
     s.topp = p.mode_topp;
     if (!p.mode_topp && !p.mode_mins) s.k_target = topk_count(row_param(p, r), s.L);
-    if (p.mode_topp && row_param(p, r) >= 1.0) {  // p = 1 keeps every eligible key
+    if (p.mode_topp && row_param(p, r) >= 1.0) {  // p = 1 keeps every eligible key, at most cap
       s.topp = 0;
-      s.k_target = s.L;
+      s.k_target = static_cast<int>(min(static_cast<int64_t>(s.L), p.cap));
+      s.clamped = s.k_target < s.L;
     }
   }
   const float c = p.qnorm[r] * p.kmax[b * p.Hkv + h / p.group];
@@ -1698,7 +1699,10 @@ __global__ __launch_bounds__(64) void k_compact(SelParams p) {
         const int nq = avail / 4;
         int4* out4 = reinterpret_cast<int4*>(out + done);
         const int4* st4 = reinterpret_cast<const int4*>(stage);
-        for (int t = lane; t < nq; t += 64) out4[t] = st4[t];
+        // The selection keeps at most cap keys; bounded all the same, so that no
+        // row can reach the next one's list (cap is a multiple of 4 here).
+        const int nst = static_cast<int>(min<int64_t>(nq, max<int64_t>(p.cap - done, 0) / 4));
+        for (int t = lane; t < nst; t += 64) out4[t] = st4[t];
         const int rem = avail - 4 * nq;
         const int carry = lane < rem ? stage[4 * nq + lane] : 0;
         wave_sync();
@@ -1722,7 +1726,7 @@ __global__ __launch_bounds__(64) void k_compact(SelParams p) {
   else run(std::false_type{});
   if (quads) {  // the last entries, fewer than 4
     wave_sync();
-    if (lane < base - done) out[done + lane] = stage[lane];
+    if (lane < base - done && done + lane < p.cap) out[done + lane] = stage[lane];
   }
   const int n = min(base, static_cast<int>(p.cap));
   if (!p.unpadded)
