@@ -329,6 +329,9 @@ __global__ __launch_bounds__(64 * W)
 #pragma unroll
     for (int e = 0; e < 4 * E4; ++e) z += static_cast<double>(term(f[e]));
     target = prm * reduce_sum(z);
+  } else if (TOPP && L > p.cap) {  // p = 1: the cap best of all keys
+    want = static_cast<int>(p.cap);
+    clamped = true;
   }
   if (!by_mass && want >= L) search = false;  // every eligible key
   while (search) {

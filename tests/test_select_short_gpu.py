@@ -118,3 +118,34 @@ def test_short_rows_in_groups_and_small_workspace(gpu):
         ws = torch.full((qp + tiles * 64 * ld * 4,), 0xFF, dtype=torch.uint8, device="cuda")
         got = va.select(tq, tk, P, "topk", 0.1, False, cap=cap, workspace=ws)
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("N,P,cap,params", [
+    (700, 1, 128, 1.0), (1000, 64, 300, 1.0), (1000, 64, 301, [0.6, 1.0]), (3000, 64, 1024, [1.0, 0.6]),
+    (3000, 64, 5, 1.0), (7000, 128, 4097, 1.0), (9000, 256, 4096, [1.0, 0.6]), (16384, 512, 16380, 1.0)])
+def test_short_topp_of_one_is_clamped_to_cap(gpu, N, P, cap, params, causal):
+    """p = 1 keeps every eligible key; a block with more than cap of them keeps its cap best (not
+    the first by index) and is counted.  One case for every shape of the row kernel."""
+    q, k, _ = synth.planted_case(N + cap, 1, 2, 1, N, 64, frac=0.03, logits=1.5)
+    head = [params, params] if np.isscalar(params) else params
+    Np = (N + P - 1) // P
+    ncl = torch.zeros(1, dtype=torch.int32, device="cuda")
+    idx, cnt = va.select(dev(q), dev(k), P, "topp", params, causal, cap=cap, n_clamped=ncl)
+    torch.cuda.synchronize()
+    L = np.minimum(N, (np.arange(Np) + 1) * P) if causal else np.full(Np, N)
+    c = cnt.cpu().numpy()[0]
+    clamped = 0
+    some = np.unique(np.linspace(0, Np - 1, 12).astype(int))
+    for h, p in enumerate(head):
+        if p == 1.0:
+            assert np.array_equal(c[h], np.minimum(L, cap))
+            clamped += int((L > cap).sum())
+        else:
+            clamped += int((c[h] == cap).sum())
+        rows = h * Np + some
+        mism = check_rows(q, k, P, oracle.TOPP, p, causal, cap,
+                          idx.reshape(-1, cap).cpu().numpy()[rows], c.reshape(-1)[rows], rows,
+                          compact=True)
+        assert mism <= 1
+    assert int(ncl.item()) == clamped
