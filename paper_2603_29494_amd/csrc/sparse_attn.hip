@@ -507,8 +507,10 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
     // without this the outputs' error against 64 bits is 0.9% larger (75k DiT
     // layer, 5 heads: 2.366e-3 against 2.344e-3).  A weight past fp32 range
     // leaves l or O infinite, which the end of the walk sees.  A careful walk
-    // has moved its references already (lim is infinite).
-    if (__any(!(tsum <= lim))) {
+    // has moved its references already (lim is infinite).  A row that is NaN does
+    // not count: for the other rows a residual of 0 or less times an infinite V
+    // is NaN where the weights' product is infinite.
+    if (__any(tsum > lim)) {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         // Opaque, so that neither the rounded weights nor the V^T operands of

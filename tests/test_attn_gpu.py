@@ -333,6 +333,30 @@ def test_references_that_move_after_the_weights(gpu, N, D, P, causal, step):
     assert np.abs(lse.cpu().numpy().astype(np.float64) - lse_ref).max() <= 3e-4
 
 
+@pytest.mark.parametrize("D,P,causal", [(128, 64, False), (64, 64, True), (128, 128, False)])
+def test_nan_query_row_leaves_infinite_values_of_its_neighbours(gpu, D, P, causal):
+    """A query row of NaN makes its own output NaN.  An infinite value of V is infinite in the
+    rows that see its key (their weights are positive), and all else is as without either."""
+    N = 200
+    q, k, v = (synth.random_bits(40 + j, (1, 1, N, D)) for j in range(3))
+    idx, cnt = random_lists(3, 1, 1, (N + P - 1) // P, N, P, causal, N, N, min_count=N)
+    o_ref, lse_ref = oracle.sparse_attn(q, k, v, idx, cnt, P, causal)
+    nan_rows, key, dim = [5, 40, 150], 3, 7
+    qn, vn = q.copy(), v.copy()
+    qn[0, 0, nan_rows] = 0x7FC0
+    vn[0, 0, key, dim] = 0x7F80                       # +infinity
+    o, lse = va.sparse_attn(dev(qn), dev(k), dev(vn), torch.from_numpy(idx).cuda(),
+                            torch.from_numpy(cnt).cuda(), P, causal, return_lse=True)
+    torch.cuda.synchronize()
+    got, l = o.float().cpu().numpy()[0, 0], lse.cpu().numpy()[0, 0]
+    assert np.isnan(got[nan_rows]).all()
+    rows = [r for r in range(N) if r not in nan_rows and (r >= key or not causal)]
+    assert np.all(got[rows, dim] == np.inf)
+    dims = [d for d in range(D) if d != dim]
+    assert np.abs(got[np.ix_(rows, dims)] - o_ref[0, 0][np.ix_(rows, dims)]).max() <= ATOL_MAX
+    assert np.abs(l[rows] - lse_ref[0, 0, rows]).max() <= LSE_TOL
+
+
 @pytest.mark.parametrize("D,P,causal", [(128, 64, True), (64, 128, True), (128, 48, False), (64, 64, False)])
 def test_packed_sequences_match_separate_calls(gpu, D, P, causal):
     """More sequences than one launch takes (32), empty ones and ragged lengths among them, K and
