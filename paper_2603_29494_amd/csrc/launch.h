@@ -72,7 +72,9 @@ hipError_t static_workspace(void** ptr);
 
 // Selection of short sequences (select_short.hip): whether a call may take it,
 // the least workspace it needs (one row tile's scores), and the workspace it
-// makes use of.
+// makes use of.  The row kernel holds a row in the registers of at most eight
+// waves, 32 keys a lane (64 spilled: 288 us for 2700 rows of 12k tokens), which
+// sets the longest row; below it launch_select takes the faster kind.
 constexpr int64_t kShortMaxN = 16384;
 bool short_select_ok(int64_t N, int32_t mode);
 size_t short_select_min_bytes(int64_t B, int64_t Hq, int64_t N, int64_t D, int32_t block);
@@ -80,7 +82,8 @@ size_t short_select_bytes(int64_t B, int64_t Hq, int64_t N, int64_t D, int32_t b
 hipError_t launch_select_short(const SelectArgs& a, hipStream_t stream);
 
 // Workspace the size query reports, and the least that a call accepts (a short
-// sequence fits either kind of selection, so the smaller of the two).
+// sequence can be done by either kind of selection, so the smaller of the two;
+// a call takes the kind that fits, or the faster one if both do).
 size_t select_workspace_bytes(int64_t B, int64_t Hq, int64_t Hkv, int64_t N, int64_t D,
                               int32_t block, int32_t mode, int64_t cap);
 size_t select_min_workspace_bytes(int64_t B, int64_t Hq, int64_t Hkv, int64_t N, int64_t D,

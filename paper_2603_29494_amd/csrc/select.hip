@@ -1793,11 +1793,55 @@ int choose_split(int64_t B, int64_t Hq, int64_t N, int32_t P) {
 
 }  // namespace
 
+// Up to kShortMaxN tokens both kinds of selection do a call, with the same lists;
+// this is whether the passes do it faster.  The row kernel works on a row at a time
+// and costs more per row than the passes, above all past 8192 keys (eight waves of
+// 32 keys a lane leave a CU two rows); the passes have more launches to start, copy
+// K once, and to clamp a minS need histograms that the row kernel does without.
+// `per_row` and `start` are the two differences in us, fitted to both kinds' times
+// of 3752 calls (1 to 72 heads, 2000 to 16384 tokens, blocks of 16 to 128, D 64 and
+// 128, causal and not, keys with and without heavy columns and frames).  Short /
+// passes, us, not causal, 64-row blocks:
+//   minS 0.3   28 heads, 12000 tokens 161 / 130; 16384 267 / 169; 5 heads, 16384 78 / 96
+//   topK 40%   28 heads, 8300 tokens 198 / 216; 16384 499 / 327
+//   topK 15%   28 heads, 16384 tokens 429 / 456; 4 x 16 heads 856 / 694
+// The kind chosen takes 0.2% (minS) and 0.6% (topK) longer in all than the faster one
+// of each call.  Under topP the passes' levels depend on the data (72 heads, 16384
+// tokens, p = 0.9: 2117 / 1355 with heavy columns, 1634 / 1899 with frames), the row
+// kernel hardly does: it keeps all but the largest calls.
+static bool passes_are_faster(int64_t B, int64_t Hq, int64_t Hkv, int64_t N, int64_t D,
+                              int32_t block, int32_t mode, int64_t cap, int32_t causal) {
+  const bool wide = N > 8192;
+  const double n = static_cast<double>(N) * 1e-3;
+  double per_row, start, kcopy;  // per 1000 rows; per call; per million elements of K
+  if (mode == kModeTopK) {
+    per_row = wide ? 23.0 + 0.4 * n : 9.0 + 0.5 * n;
+    start = wide ? 160.0 : 150.0;
+    kcopy = 0.8;
+  } else if (mode == kModeTopP) {
+    if (!wide) return false;
+    per_row = (17.6 + 2.15 * n) * (causal ? 0.75 : 1.0);
+    start = 860.0;
+    kcopy = 1.7;
+  } else {
+    if (cap < N) return false;
+    per_row = wide ? 12.0 + 0.65 * n : 1.3 * n;
+    start = causal ? 95.0 : 80.0;
+    kcopy = 0.6;
+  }
+  const double rows = static_cast<double>(B * Hq) * static_cast<double>((N + block - 1) / block);
+  const double k = static_cast<double>(B * Hkv) * static_cast<double>(N * D);
+  return rows * 1e-3 * per_row > start + kcopy * 1e-6 * k;
+}
+
+// The causal bit is not known here: room for the passes wherever some call of these
+// shapes takes them.
 size_t select_workspace_bytes(int64_t B, int64_t Hq, int64_t Hkv, int64_t N, int64_t D,
                               int32_t block, int32_t mode, int64_t cap) {
-  (void)cap;
-  if (short_select_ok(N, mode)) return short_select_bytes(B, Hq, N, D, block);
-  return layout(B, Hq, Hkv, N, D, block, choose_split(B, Hq, N, block), mode == 1).total;
+  const size_t passes = layout(B, Hq, Hkv, N, D, block, choose_split(B, Hq, N, block), mode == 1).total;
+  if (!short_select_ok(N, mode)) return passes;
+  const size_t rows = short_select_bytes(B, Hq, N, D, block);
+  return passes_are_faster(B, Hq, Hkv, N, D, block, mode, cap, 0) ? std::max(rows, passes) : rows;
 }
 
 size_t select_min_workspace_bytes(int64_t B, int64_t Hq, int64_t Hkv, int64_t N, int64_t D,
@@ -1819,15 +1863,17 @@ void score_pass(int64_t D, bool topp, dim3 grid, const SelParams& p, hipStream_t
 }
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
-  if (short_select_ok(a.q.N, a.mode) &&
-      a.workspace_bytes >= short_select_min_bytes(a.q.B, a.q.H, a.q.N, a.q.D, a.block))
-    return launch_select_short(a, stream);
   const int64_t B = a.q.B, Hq = a.q.H, Hkv = a.k.H, N = a.q.N, D = a.q.D;
   const int32_t P = a.block;
   const int64_t Np = (N + P - 1) / P;
   const int64_t rows = B * Hq * Np;
   const int split = choose_split(B, Hq, N, P);
   const Layout l = layout(B, Hq, Hkv, N, D, P, split, a.mode == 1);
+  if (short_select_ok(N, a.mode) && a.workspace_bytes >= short_select_min_bytes(B, Hq, N, D, P)) {
+    if (a.workspace_bytes < l.total ||
+        !passes_are_faster(B, Hq, Hkv, N, D, P, a.mode, a.cap, a.causal))
+      return launch_select_short(a, stream);
+  }
   if (a.workspace_bytes < l.total) return hipErrorInvalidValue;
   char* ws = static_cast<char*>(a.workspace);
   SelParams p{};

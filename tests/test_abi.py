@@ -316,6 +316,26 @@ def test_workspace_counts_kv_heads_once():
     assert lib.vecattn_select_workspace_bytes(ctypes.byref(q), ctypes.byref(q), 0, 0, 3277) == 0
 
 
+@pytest.mark.parametrize("mode,block", [("topk", 16), ("topp", 8), ("mins", 16)])
+def test_workspace_has_room_for_the_passes_where_they_are_faster(mode, block):
+    # 28 heads of 8300 keys in small blocks: the scores of short sequences need at most 128 MiB
+    # (and the pooled queries), the passes more than 10 KB a block (1024 candidates, 128 bins,
+    # two bitmasks).  A clamped minS stays with the short kind, as does a call of few blocks.
+    size = _lib.load().vecattn_select_workspace_bytes
+    m = _lib.mode_id(mode)
+    q, k = desc(1, 28, 8300, 64), desc(1, 4, 8300, 64)
+    rows = 28 * ((8300 + block - 1) // block)
+    passes = rows * (8 * 1024 + 4 * 128 + 2 * 4 * 260)
+    short = (128 << 20) + rows * 128 + 256
+    assert passes > short
+    assert size(ctypes.byref(q), ctypes.byref(k), block, m, 8300) >= passes
+    if mode == "mins":
+        assert size(ctypes.byref(q), ctypes.byref(k), block, m, 8299) <= short
+    few = desc(1, 4, 8300, 64)                        # 130 blocks a head: three tiles of 64
+    short = 4 * 3 * 64 * 8320 * 4 + 4 * 130 * 128 + 256
+    assert size(ctypes.byref(few), ctypes.byref(few), 64, m, 8300) <= short
+
+
 def test_head_sparsity_and_recall_reject_bad_arguments():
     lib = _lib.load()
 

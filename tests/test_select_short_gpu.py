@@ -149,3 +149,41 @@ def test_short_topp_of_one_is_clamped_to_cap(gpu, N, P, cap, params, causal):
                           compact=True)
         assert mism <= 1
     assert int(ncl.item()) == clamped
+
+
+@pytest.mark.parametrize("mode,param,Hq,N,P,D,causal,keep_diag,capdiv", [
+    ("mins", 0.3, 12, 9001, 16, 64, False, False, 1), ("mins", 0.7, 28, 16384, 64, 128, True, False, 1),
+    ("mins", float("inf"), 12, 9001, 16, 64, True, True, 1),
+    ("topk", 0.4, 12, 8193, 12, 64, False, False, 1), ("topk", 0.1, 28, 16383, 32, 128, True, True, 1),
+    ("topk", [0.02, 0.9, 0.5, 1.0], 4, 8000, 2, 64, False, False, 1),
+    ("topp", 0.9, 12, 12345, 6, 64, False, False, 1), ("topp", 0.6, 28, 9000, 7, 128, True, True, 1),
+    ("topp", [0.5, 1.0, 0.9, 0.99], 4, 8200, 1, 64, False, False, 5)])
+def test_both_kinds_agree_where_the_passes_are_faster(gpu, mode, param, Hq, N, P, D, causal, keep_diag, capdiv):
+    """Calls of up to 16384 tokens with so many blocks that the passes are faster: with the workspace
+    of the size query they run (behind the pooled queries they leave a row's last phase, 3 or 4,
+    where the short kind has a score), with one row tile's scores the short kind does.  Lists, counts and clamped blocks are equal; by mass, at most one
+    block in fifty may differ (the same terms in another order)."""
+    q, k, _ = synth.planted_case(N + P, 1, Hq, 2 if Hq == 4 else 4, N, D, frac=0.04, logits=2.0)
+    k[0, 0, 5::7] = k[0, 0, 5]        # exact ties
+    tq, tk = dev(q), dev(k)
+    cap = max(1, va.max_count(N, P, causal, mode, param, keep_diag) // capdiv)
+    Np = (N + P - 1) // P
+    out = []
+    big = va.workspace_bytes(tq, tk, P, causal, mode, cap)
+    pooled = -(-(Hq * Np * D * 2) // 256) * 256
+    tile = min(Np, 64) * (-(-N // 32) * 32) * 4
+    for size in (big, pooled + tile):
+        ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+        ncl = torch.zeros(1, dtype=torch.int32, device="cuda")
+        idx, cnt = va.select(tq, tk, P, mode, param, causal, cap=cap, workspace=ws, n_clamped=ncl,
+                             keep_diag=keep_diag)
+        out.append((idx, cnt, ncl))
+        torch.cuda.synchronize()
+        assert (int(ws[pooled:pooled + 4].view(torch.int32)) in (3, 4)) == (size == big)
+        del ws
+    assert va.check_lists(out[0][0], out[0][1], N) == 0
+    same = (out[0][0] == out[1][0]).all(-1) & (out[0][1] == out[1][1])
+    bad = int((~same).sum())
+    assert bad == 0 or (mode == "topp" and bad * 50 <= same.numel()), bad
+    assert abs(int(out[0][2]) - int(out[1][2])) <= bad
+    assert capdiv == 1 or int(out[0][2]) > 0
