@@ -120,9 +120,11 @@ vecattn_status vecattn_select_max_count(int64_t N, int32_t block, int32_t causal
                                         double param, int64_t* out);
 
 /*
- * Workspace bytes vecattn_select needs for these shapes (device memory the
- * caller allocates and passes in; contents need not be initialised).  The
- * size depends on B, Hq, Hkv (kd->H), N, D and block.
+ * Workspace bytes vecattn_select makes use of for these shapes (device memory
+ * the caller allocates and passes in; contents need not be initialised).  The
+ * size depends on B, Hq, Hkv (kd->H), N, D, block and mode, and for minS on
+ * whether cap is below N; it does not depend on the causal bits.  Calls with
+ * less are described at vecattn_select.
  * Errors: INVALID_ARG (a NULL pointer, block < 1, cap < 1, an unknown mode,
  * sizes < 1 or N > 2^30, Hq % Hkv != 0, D not in {64, 128}).
  */
@@ -151,7 +153,14 @@ size_t vecattn_select_workspace_bytes(const vecattn_tdesc* qd, const vecattn_tde
  *            whose threshold-mode selection exceeded cap is ADDED to it
  *            (topP and minS blocks keep their cap highest-scoring keys;
  *            cross-tile minS blocks their first cap keys).
- *   workspace : device memory of at least vecattn_select_workspace_size bytes.
+ *   workspace : device memory (16-byte aligned), vecattn_select_workspace_size
+ *            bytes for the best speed.  A call of at most 16384 tokens (topK,
+ *            topP, minS) also runs in less, with the same lists (topP cuts whose
+ *            mass is within fp32 rounding of p aside), but no less than
+ *              align256(B * Hq * N_p * D * 2)
+ *                + min(N_p, 64) * 4 * (N rounded up to a multiple of 32)
+ *            (or than that size, if it is smaller); longer sequences and
+ *            cross-tile minS need the whole size.
  * Errors: INVALID_ARG (null pointer, shape mismatch between q and k, block < 1,
  * param outside (0, 1] for topK / topP or negative / NaN for minS, cap < 1);
  * CAPACITY (topK with cap < max_i k_i, or a workspace that is too small);
@@ -172,9 +181,10 @@ vecattn_status vecattn_select(const void* q, const vecattn_tdesc* qd, const void
  * are those of vecattn_select.  Every call on a GPU uses that GPU's one copy
  * (the current device's): calls that overlap on one GPU (other streams, other
  * threads) race and must be serialised by the caller.
- * Errors: as vecattn_select; CAPACITY when vecattn_select_workspace_size for
- * these shapes exceeds VECATTN_STATIC_WORKSPACE_BYTES; DEVICE if the array's
- * device address cannot be obtained.
+ * Errors: as vecattn_select; CAPACITY when these shapes need a workspace of
+ * more than VECATTN_STATIC_WORKSPACE_BYTES (the least vecattn_select accepts,
+ * not the size query's); DEVICE if the array's device address cannot be
+ * obtained.
  */
 #define VECATTN_STATIC_WORKSPACE_BYTES (64u << 20)
 vecattn_status vecattn_select_noalloc(const void* q, const vecattn_tdesc* qd, const void* k,
@@ -330,16 +340,19 @@ vecattn_status vecattn_check_lists(const int32_t* idx, int64_t rows, int64_t cap
  * B = 1 tensors: sequence s is rows [cu_seqlens[s], cu_seqlens[s+1]) (host
  * int64, nseq + 1 values, cu_seqlens[0] = 0, non-decreasing, last = N; empty
  * sequences are allowed).  Each sequence is handled exactly as a separate
- * B = 1 call on its rows (its key indices count from its first row); the
- * calls run one after another on `stream`.  Output layouts are the
+ * B = 1 call on its rows (its key indices count from its first row).  The
+ * selections run one after another on `stream`; the attention takes up to 32
+ * sequences per launch, the longest first.  Output layouts are the
  * per-sequence arrays laid end to end:
  *   idx    : int32, for each sequence [Hq, N_p(s), cap], N_p(s) = ceil(n_s / P)
  *   counts : int32, for each sequence [Hq, N_p(s)]
  *   lse    : fp32,  for each sequence [Hq, n_s] (optional)
  * Q, K, V, O rows are read and written in place (the [1, H, N, D] views).
- * The selection workspace must be sized (vecattn_select_workspace_size) for
- * the longest sequence.  Every argument is checked for every sequence before
- * the first launch.  Many short sequences cost one set of launches each.
+ * The selection workspace is sized (vecattn_select_workspace_size) for the
+ * longest sequence; what vecattn_select says of less holds for each one.
+ * Every argument is checked for every sequence before the first launch.  Each
+ * sequence costs the selection a set of launches of its own (three up to 16384
+ * tokens, about 25 beyond).
  */
 vecattn_status vecattn_select_varlen(const void* q, const vecattn_tdesc* qd, const void* k,
                                      const vecattn_tdesc* kd, const int64_t* cu_seqlens,

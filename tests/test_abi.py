@@ -316,6 +316,30 @@ def test_workspace_counts_kv_heads_once():
     assert lib.vecattn_select_workspace_bytes(ctypes.byref(q), ctypes.byref(q), 0, 0, 3277) == 0
 
 
+@pytest.mark.parametrize("mode", [0, 1, 2, 3])
+@pytest.mark.parametrize("N,block,D", [(1000, 64, 128), (5000, 48, 64), (16384, 64, 128), (16385, 64, 128)])
+def test_select_workspace_below_the_least_is_refused(N, block, D, mode):
+    # The least workspace of a short sequence is one tile's scores behind the pooled queries; the
+    # size query's is never below it, and is the least for longer ones and for cross-tile minS.
+    lib = _lib.load()
+    q, k = desc(1, 4, N, D), desc(1, 2, N, D)
+    size = lib.vecattn_select_workspace_bytes(ctypes.byref(q), ctypes.byref(k), block, mode, N)
+    blocks = (N + block - 1) // block
+    least = -(-4 * blocks * D * 2 // 256) * 256 + min(blocks, 64) * 4 * (-(-N // 32) * 32)
+    if mode == 3 or N > 16384:
+        least = size
+    assert least <= size
+
+    def call(nbytes):
+        return lib.vecattn_select(FAKE, ctypes.byref(q), FAKE, ctypes.byref(k), block, 0, mode, 0.5,
+                                  FAKE, N, FAKE, None, FAKE, nbytes, None)
+
+    assert call(least - 1) == CAPACITY and call(0) == CAPACITY
+    # enough: the next check (the workspace's alignment) is reached
+    assert lib.vecattn_select(FAKE, ctypes.byref(q), FAKE, ctypes.byref(k), block, 0, mode, 0.5,
+                              FAKE, N, FAKE, None, FAKE + 8, least, None) == INVALID
+
+
 @pytest.mark.parametrize("mode,block", [("topk", 16), ("topp", 8), ("mins", 16)])
 def test_workspace_has_room_for_the_passes_where_they_are_faster(mode, block):
     # 28 heads of 8300 keys in small blocks: the scores of short sequences need at most 128 MiB

@@ -3,8 +3,8 @@ for callers that cannot allocate device memory), through the C ABI: its lists
 and counts equal vecattn_select's on the same inputs (the same kernels on a
 workspace the library holds), also on a second, smaller call right after the
 first (the workspace keeps the first call's contents), and follow the oracle's
-selection rule; shapes whose workspace exceeds the library's 64 MiB are
-rejected."""
+selection rule; shapes that need more than the library's 64 MiB are rejected,
+shapes that would merely use more are not."""
 import numpy as np
 import pytest
 import torch
@@ -51,6 +51,21 @@ def test_noalloc_matches_select_twice_in_a_row(gpu, pair):
         mism = check_rows(q, k, block, omode, param, causal, cap, idx.cpu().numpy(),
                           cnt.cpu().numpy(), rows)
         assert mism <= max(1, len(rows) // 20)
+
+
+@pytest.mark.parametrize("mode,param", [("topk", 0.1), ("topp", 0.8), ("mins", 0.5)])
+def test_noalloc_takes_shapes_that_would_use_more(gpu, mode, param):
+    # 24 heads x 8000 keys: the size query asks for all scores, 64 MiB hold two thirds of them.
+    q, k, _ = synth.planted_case(830, 1, 24, 2, 8000, 64)
+    tq, tk = dev(q), dev(k)
+    cap = _lib.max_count(8000, 64, True, mode, param)
+    assert _lib.workspace_bytes(tq, tk, 64, True, mode, cap) > _lib.STATIC_WORKSPACE_BYTES
+    idx = torch.full((1, 24, 125, cap), 7, dtype=torch.int32, device="cuda")
+    cnt = torch.full((1, 24, 125), 7, dtype=torch.int32, device="cuda")
+    _lib.select_noalloc(tq, tk, 64, mode, param, True, cap, idx, cnt)
+    ref_i, ref_c = _lib.select(tq, tk, 64, mode, param, True, cap=cap)
+    torch.cuda.synchronize()
+    assert torch.equal(cnt, ref_c) and torch.equal(idx, ref_i)
 
 
 def test_noalloc_rejects_workspace_beyond_limit(gpu):
