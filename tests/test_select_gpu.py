@@ -1,6 +1,8 @@
 """GPU parity of important-vector selection (Sec. 3.1: pooled-query scores,
 row-wise topK / topP, minS of Eq. 3 and Algorithm 1's cross-tile minS) against
-the oracle, through the C ABI.  The index-set rule is in selection_parity.py."""
+the oracle, through the C ABI.  The index-set rule is in selection_parity.py.
+Up to 16384 tokens the kernels for short sequences do topK, topP and minS; what is
+tested here of those modes is tested of the passes in test_select_passes_gpu.py."""
 import numpy as np
 import pytest
 import torch

@@ -47,7 +47,7 @@ def test_short_equals_passes(long_layer, n, P, D, mode, param):
     for keep_diag in (False, True):
         cap = va.max_count(LONG, P, True, mode, param, keep_diag)
         Np = (n + P - 1) // P
-        whole = n // P                     # blocks of P rows in both sequences
+        whole = n // P  # blocks of P rows in both sequences (the ragged ones: the oracle, below)
         # the longer sequence selected only as far as the short one's whole blocks reach
         il, cl = va.select(q, k, P, mode, param, True, cap=cap, keep_diag=keep_diag)
         i_s, c_s = va.select(q[:, :, :n], k[:, :, :n], P, mode, param, True, cap=cap,
@@ -66,7 +66,11 @@ def test_short_equals_passes(long_layer, n, P, D, mode, param):
     (1000, 1, 5, "topk", 0.1, None), (1000, 1, 5, "topp", 0.9, None),       # one wave per row
     (2500, 1, 2, "topk", 0.2, None), (2500, 1, 2, "topp", 0.95, 777),
     (2500, 1, 2, "mins", 2.0, 301),
-    (700, 64, 2, "topp", 0.95, 130), (5000, 64, 2, "topp", 0.9, 401), (5000, 64, 2, "mins", 3.0, 1022)])
+    (700, 64, 2, "topp", 0.95, 130), (5000, 64, 2, "topp", 0.9, 401), (5000, 64, 2, "mins", 3.0, 1022),
+    (1, 64, 2, "topk", 0.5, None), (1, 1, 3, "topp", 0.5, None), (1, 64, 2, "mins", 0.0, None),
+    (8000, 64, 2, "topk", 0.3, None), (12345, 64, 2, "topk", 0.2, None), (12345, 128, 2, "topp", 0.9, None),
+    (12345, 64, 2, "mins", 0.7, None), (12345, 128, 2, "topp", 0.95, 3001), (16383, 128, 1, "topp", 0.6, None),
+    (16383, 128, 1, "mins", 2.0, 2222)])
 def test_short_matches_oracle_with_caps(gpu, N, P, Hq, mode, param, cap):
     q, k, _ = synth.planted_case(N + P, 1, Hq, 1, N, 64, frac=0.03, logits=1.5)
     full = va.max_count(N, P, False, mode, param)
@@ -87,6 +91,25 @@ def test_short_matches_oracle_with_caps(gpu, N, P, Hq, mode, param, cap):
         _, whole = va.select(dev(q), dev(k), P, mode, param, False, cap=full)
         assert int(ncl.item()) == int((whole > cap).sum()) > 0
         assert torch.equal(cnt, whole.clamp(max=cap))
+
+
+@pytest.mark.parametrize("mode,param", CASES)
+@pytest.mark.parametrize("n,P,D", [(1, 64, 64), (63, 64, 128), (1000, 16, 128), (1025, 64, 128),
+                                   (4097, 64, 128), (8191, 48, 64), (8193, 64, 128), (16383, 64, 64)])
+def test_short_last_blocks_match_oracle(long_layer, n, P, D, mode, param):
+    """The ragged last block, whose rows another length does not share, and the one before it."""
+    tq, tk = (x[:, :, :n].contiguous() for x in long_layer[D])
+    q, k = (x.view(torch.int16).cpu().numpy().view(np.uint16) for x in (tq, tk))
+    Np = (n + P - 1) // P
+    rows = np.array([h * Np + i for h in range(2) for i in range(max(0, Np - 2), Np)])
+    om = {"topk": oracle.TOPK, "topp": oracle.TOPP, "mins": oracle.MINS}[mode]
+    for causal in (False, True):
+        cap = va.max_count(n, P, causal, mode, param)
+        idx, cnt = va.select(tq, tk, P, mode, param, causal, cap=cap)
+        torch.cuda.synchronize()
+        mism = check_rows(q, k, P, om, param, causal, cap, idx.reshape(-1, cap).cpu().numpy()[rows],
+                          cnt.reshape(-1).cpu().numpy()[rows], rows, compact=True)
+        assert mism <= 1
 
 
 @pytest.mark.parametrize("bad", ["nan", "inf", "-inf", "huge"])
