@@ -2,16 +2,17 @@
 // Algorithm 1) for gfx950: row-wise topK (a budget), topP (a cumulative
 // softmax-mass threshold) and minS (Eq. 3: within alpha of the row maximum)
 // over the estimated map Q_p K^T / sqrt(D), without ever writing that map to
-// memory (the TilingSelect principle, Sec. 3.1.3).
+// memory (the TilingSelect principle, Sec. 3.1.3).  Sequences of up to 16384
+// tokens and few rows take select_short.hip instead, which does write it.
 //
 // Exact selection needs the score of the k-th key (topK) or of the key where
 // the mass reaches p (topP).  Every row therefore narrows a score interval
 // that must contain its cut, one pass over the keys at a time:
 //   HIST     score tiles stay on chip; each key of the row is classified
 //            against the interval (above / inside / below); keys inside land
-//            in a 128-bin LDS histogram, keys above are counted (and their
-//            softmax mass summed for topP).  A resolve kernel picks the bin
-//            range that must hold the cut, which becomes the next interval.
+//            in a 128-bin LDS histogram, keys above are counted (topP: the
+//            first pass also sums each bin's softmax mass).  A resolve kernel
+//            picks the bin range that must hold the cut, the next interval.
 //   COLLECT  once the interval holds at most kCand keys: a bit per key at or
 //            above the interval, and the (score, index) pairs of the keys
 //            inside it; a resolve kernel ranks those candidates, fixes the cut

@@ -13,9 +13,10 @@
 // A long row must not be written to memory (75k tokens, 40 heads: 14 GB of
 // scores against 1.5 GB of keys), but a short sequence's scores stay in the
 // last-level cache, and the passes' 23 launches, most of them idle or waiting
-// for the one before, cost more than they save.  Row tiles are taken in groups
-// whose scores fit the workspace (at most kShortScoreBytes), one pair of
-// launches per group.
+// for the one before, cost more than they save; on many rows they save more,
+// and launch_select takes them (passes_are_faster in select.hip).  Row tiles are
+// taken in groups whose scores fit the workspace (at most kShortScoreBytes), one
+// pair of launches per group.
 #include <float.h>
 
 #include <algorithm>
