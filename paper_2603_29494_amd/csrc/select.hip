@@ -1803,7 +1803,7 @@ int choose_split(int64_t B, int64_t Hq, int64_t N, int32_t P) {
 // of 3752 calls (1 to 72 heads, 2000 to 16384 tokens, blocks of 16 to 128, D 64 and
 // 128, causal and not, keys with and without heavy columns and frames).  Short /
 // passes, us, not causal, 64-row blocks:
-//   minS 0.3   28 heads, 12000 tokens 161 / 130; 16384 267 / 169; 5 heads, 16384 78 / 96
+//   minS 0.3   28 heads, 12000 tokens 161 / 130; 16384 267 / 169; 5 heads, 16384 58 / 118
 //   topK 40%   28 heads, 8300 tokens 198 / 216; 16384 499 / 327
 //   topK 15%   28 heads, 16384 tokens 429 / 456; 4 x 16 heads 856 / 694
 // The kind chosen takes 0.2% (minS) and 0.6% (topK) longer in all than the faster one
