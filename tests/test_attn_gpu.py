@@ -70,7 +70,8 @@ def test_pool_bit_exact(gpu, N, P, D):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("N,P", [(100, 31), (100, 32), (95, 33), (1000, 64), (33, 64), (1999, 1000)])
+@pytest.mark.parametrize("N,P", [(100, 31), (100, 32), (95, 33), (1000, 64), (33, 64), (1999, 1000),
+                                 (200, 63), (333, 80), (500, 100), (311, 127)])
 def test_pool_row_groups_bit_exact(gpu, N, P, D):
     """Both sides of the block size from which a wave shares a block's rows, and ragged ends."""
     q = synth.random_bits(N + P, (2, 2, N, D), scale=3.0)
