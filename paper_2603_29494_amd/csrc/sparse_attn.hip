@@ -38,8 +38,13 @@ constexpr int kTile = 64;     // keys per gathered tile
 // Progress of this kernel's workgroups on each XCD since the library was
 // loaded, in units of 1/kHerdUnit of a list (wraps at 2^32).  It paces the
 // tile order below: a locality hint only, so concurrent calls sharing it
-// affect speed, never results.
-__device__ unsigned int g_herd[8];
+// affect speed, never results.  Each XCD's counter has cache lines of its own:
+// with all eight in one line the chip's updates serialised, ~21 ns each, which
+// bounded launches of short lists (40 heads, 40 packed sequences of 700 tokens,
+// two tiles a list: 701 us, 420 apart; 4 x 12 heads, 4096 tokens, 13 tiles: 104,
+// 75; 24 heads, 24001 tokens, 75 tiles: 1545, 1509).
+constexpr int kHerdStride = 64;
+__device__ __align__(256) unsigned int g_herd[8 * kHerdStride];
 constexpr int kHerdUnit = 4096;
 // Tiles per update of that counter: updates to one address serialise in L2,
 // so they must be rare next to the gathers.
@@ -220,7 +225,8 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
   if (threadIdx.x == 0 && !herd) s_rot = 0;
   if (threadIdx.x == 0 && herd) {
     const unsigned int progress =
-        __hip_atomic_load(&g_herd[xcd], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_load(&g_herd[xcd * kHerdStride], __ATOMIC_RELAXED,
+                          __HIP_MEMORY_SCOPE_AGENT);
     const unsigned int at = (progress / static_cast<unsigned int>(herd_slots)) % kHerdUnit;
     // ntiles <= 2^18 (count <= N < 2^24), so the product fits 32 bits.
     s_rot = static_cast<int>((at * static_cast<unsigned int>(ntiles)) / kHerdUnit);
@@ -381,8 +387,9 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     if (herd && !careful && wave == 0 && lane == 0 && (t % kHerdBatch) == kHerdBatch - 1)
-      __hip_atomic_fetch_add(&g_herd[xcd], herd_units(t + 1) - herd_units(t + 1 - kHerdBatch),
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_add(&g_herd[xcd * kHerdStride],
+                             herd_units(t + 1) - herd_units(t + 1 - kHerdBatch), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
     if (MORE) stage_ids(t + 1, st ^ 1);
 
     // S^T = K_tile Q^T for this wave's 32 keys x 32 rows, and between its MFMAs
@@ -583,7 +590,7 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
   }
 
   if (herd && wave == 0 && lane == 0 && ntiles % kHerdBatch != 0)
-    __hip_atomic_fetch_add(&g_herd[xcd], kHerdUnit - herd_units(ntiles - ntiles % kHerdBatch),
+    __hip_atomic_fetch_add(&g_herd[xcd * kHerdStride], kHerdUnit - herd_units(ntiles - ntiles % kHerdBatch),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
   // Merge the two key halves (kw = 1 hands its state to kw = 0 through LDS).
