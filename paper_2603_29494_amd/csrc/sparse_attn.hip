@@ -272,23 +272,6 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
   const int rw = wave % RG;
   const int kw = wave / RG;
 
-  // Q^T operand: this lane's query row, head-dim slots 16s + 8g .. +7.
-  const int my_row = row0 + 32 * rw + ln;
-  bf16x8 qf[DS];
-  {
-    const bool have = my_row < row_end;
-    const u32x4* qr = reinterpret_cast<const u32x4*>(
-        q + b * q_sB + h * q_sH + static_cast<int64_t>(have ? my_row : row0) * q_sN);
-#pragma unroll
-    for (int s = 0; s < DS; ++s) {
-      const u32x4 t = have ? qr[2 * s + g] : u32x4{0, 0, 0, 0};
-      qf[s] = __builtin_bit_cast(bf16x8, t);
-    }
-    // Retire the Q loads here, so that the compiler's wait analysis does not
-    // make the first MFMA of every tile wait for the gathers in flight.
-    wait_vmcnt<0>();
-  }
-
   // Gather mapping: direct-load instruction u of this wave covers LDS chunks
   // [(wave*U + u)*64, +64) of a tile; lane -> (row r, physical chunk x), and
   // it fetches logical chunk x ^ swz(r) of key row ids[r].
@@ -343,6 +326,25 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
       ids_to_lds(tile_rsrc(t), static_cast<uint32_t>(lane) * 4u, ibuf(st));
   };
 
+  // Q^T operand: this lane's query row, head-dim slots 16s + 8g .. +7.  The first
+  // tile's ids are on their way already, and its gathers follow as soon as they
+  // are here: the first step's wait covers Q as well, where Q, ids and gathers
+  // one after another cost a list of two tiles 4% (28 heads, 8192 tokens, causal,
+  // 1% of the keys: 62.0 -> 59.5 us; 10%: 106, 102).
+  if (ntiles > 0) load_ids(0);
+  const int my_row = row0 + 32 * rw + ln;
+  bf16x8 qf[DS];
+  {
+    const bool have = my_row < row_end;
+    const u32x4* qr = reinterpret_cast<const u32x4*>(
+        q + b * q_sB + h * q_sH + static_cast<int64_t>(have ? my_row : row0) * q_sN);
+#pragma unroll
+    for (int s = 0; s < DS; ++s) {
+      const u32x4 t = have ? qr[2 * s + g] : u32x4{0, 0, 0, 0};
+      qf[s] = __builtin_bit_cast(bf16x8, t);
+    }
+  }
+
   f32x16 oacc[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) oacc[db] = f32x16{};
@@ -354,6 +356,7 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
   int settled = 0;      // every row of the wave has a reference
   float lim = 256.0f;   // a tile sum above it moves references after the weights
   int careful = 0;      // second walk: references are fixed before the weights
+  int moved = 0;        // some tile of this wave had weights above 256
 
   // Per-lane byte offsets of the LDS reads inside a stage, opaque to the
   // compiler so that each stage's address is a constant offset from them (one
@@ -518,6 +521,7 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
     // not count: for the other rows a residual of 0 or less times an infinite V
     // is NaN where the weights' product is infinite.
     if (__any(tsum > lim)) {
+      moved = 1;
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         // Opaque, so that neither the rounded weights nor the V^T operands of
@@ -545,16 +549,16 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
   // The walk, at most twice: a score more than ~119 (log2 units) above its
   // row's reference overflows a weight, which a test of every weight before
   // P V would catch in time (as the first tile does) at the price of the
-  // softmax running beside no MFMA.  So O and l are tested once, at the end:
-  // anything not finite in the workgroup sends all of it through the list
-  // again with the references fixed before the weights.  Such a list costs
+  // softmax running beside no MFMA.  So O and l of a wave that met weights above
+  // 256 (the others' are what a second walk would find) are tested once, at the
+  // end: anything not finite sends the whole workgroup through the list again
+  // with the references fixed before the weights.  Such a list costs
   // twice: 24 heads, 24001 tokens, a fifth of the keys, one key of every list
   // 200 nats above the others: 1.56 -> 3.26 ms (causal 0.81 -> 1.60, three
   // quarters of the blocks), where a test before each P V took 1.64 (0.88) and
   // 1.66 (0.90) on lists without such a key.
   for (;;) {
     if (ntiles > 0) {
-      load_ids(0);
 #pragma unroll
       for (int n = 0; n < 2 * U; ++n) gather(n, 0);
       stage_ids(0, 0);
@@ -571,15 +575,17 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
     } else if (t < ntiles) {
       step(t, 0, std::false_type{});
     }
-    if (careful) break;
-    float fin = l_run * 0.0f;  // 0, or NaN once anything is not finite
+    if (moved && !careful) {
+      float fin = l_run * 0.0f;  // 0, or NaN once anything is not finite
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+      for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) fin = __builtin_fmaf(oacc[db][e], 0.0f, fin);
-    if (__any(fin != 0.0f) && lane == 0) s_redo = 1;
+        for (int e = 0; e < 16; ++e) fin = __builtin_fmaf(oacc[db][e], 0.0f, fin);
+      if (__any(fin != 0.0f) && lane == 0) s_redo = 1;
+    }
+    wait_vmcnt<0>();  // no gather may still be landing in the buffers the merge reuses
     __syncthreads();
-    if (!__builtin_amdgcn_readfirstlane(s_redo)) break;
+    if (careful || !__builtin_amdgcn_readfirstlane(s_redo)) break;
     careful = 1;
     lim = INFINITY;
     settled = 0;
@@ -587,6 +593,7 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
     l_run = 0.0f;
 #pragma unroll
     for (int db = 0; db < DB; ++db) oacc[db] = f32x16{};
+    if (ntiles > 0) load_ids(0);
   }
 
   if (herd && wave == 0 && lane == 0 && ntiles % kHerdBatch != 0)
@@ -595,8 +602,6 @@ __global__ __launch_bounds__(4 * ROWS) __attribute__((amdgpu_waves_per_eu(2))) v
 
   // Merge the two key halves (kw = 1 hands its state to kw = 0 through LDS).
   l_run += __shfl_xor(l_run, 32);
-  wait_vmcnt<0>();  // no gather may still be landing in the buffers reused below
-  __syncthreads();
   // Reuse the tile buffers (each holds one row group's 32 x D fp32 O).
   float* red_o = reinterpret_cast<float*>(rw == 0 ? k_s0 : rw == 1 ? v_s0 : rw == 2 ? k_s1 : v_s1);
   float* red_ml = s_ml[rw];

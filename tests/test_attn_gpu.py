@@ -334,6 +334,35 @@ def test_references_that_move_after_the_weights(gpu, N, D, P, causal, step):
     assert np.abs(lse.cpu().numpy().astype(np.float64) - lse_ref).max() <= 3e-4
 
 
+@pytest.mark.parametrize("row", [0, 33, 63, 100])
+@pytest.mark.parametrize("D,P,causal", [(128, 64, False), (64, 64, True), (128, 128, True), (64, 128, False)])
+def test_one_row_overflows_its_weights(gpu, D, P, causal, row):
+    """One query row's scores rise by 110 nats from tile to tile, those of all others hardly: the
+    waves of its workgroup that met no large weight walk the list again with the one that did.
+    LSE as above (up to 6 x 110 nats)."""
+    N = 450
+    r = np.random.Generator(np.random.PCG64(D + P + row))
+    u = r.standard_normal(D)
+    u /= np.linalg.norm(u)
+    q = 0.02 * r.standard_normal((1, 2, N, D))
+    q -= (q @ u)[..., None] * u
+    q[0, :, row::200] = math.sqrt(D) * u
+    k = r.standard_normal((1, 1, N, D)) * 0.5
+    k[0, 0] += (110.0 * (np.arange(N) // 64))[:, None] * u
+    qb, kb = synth.to_bf16_bits(q.astype(np.float32)), synth.to_bf16_bits(k.astype(np.float32))
+    vb = synth.random_bits(6, (1, 1, N, D))
+    idx, cnt = random_lists(9, 1, 2, (N + P - 1) // P, N, P, causal, N, N, min_count=N)
+    o_ref, lse_ref = oracle.sparse_attn(qb, kb, vb, idx, cnt, P, causal)
+    o, lse = va.sparse_attn(dev(qb), dev(kb), dev(vb), torch.from_numpy(idx).cuda(),
+                            torch.from_numpy(cnt).cuda(), P, causal, return_lse=True)
+    torch.cuda.synchronize()
+    got = o.float().cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    err = np.abs(got - o_ref)
+    assert err.max() <= ATOL_MAX and err.mean() <= ATOL_MEAN, (err.max(), err.mean())
+    assert np.abs(lse.cpu().numpy().astype(np.float64) - lse_ref).max() <= 3e-4
+
+
 @pytest.mark.parametrize("D,P,causal", [(128, 64, False), (64, 64, True), (128, 128, False)])
 def test_nan_query_row_leaves_infinite_values_of_its_neighbours(gpu, D, P, causal):
     """A query row of NaN makes its own output NaN.  An infinite value of V is infinite in the
