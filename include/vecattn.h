@@ -156,7 +156,8 @@ size_t vecattn_select_workspace_bytes(const vecattn_tdesc* qd, const vecattn_tde
  *   workspace : device memory (16-byte aligned), vecattn_select_workspace_size
  *            bytes for the best speed.  A call of at most 16384 tokens (topK,
  *            topP, minS) also runs in less, with the same lists (topP cuts whose
- *            mass is within fp32 rounding of p aside), but no less than
+ *            mass is within fp32 rounding of p, and NaN scores, aside), but
+ *            no less than
  *              align256(B * Hq * N_p * D * 2)
  *                + min(N_p, 64) * 4 * (N rounded up to a multiple of 32)
  *            (or than that size, if it is smaller); longer sequences and

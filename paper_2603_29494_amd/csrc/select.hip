@@ -1794,7 +1794,8 @@ int choose_split(int64_t B, int64_t Hq, int64_t N, int32_t P) {
 
 }  // namespace
 
-// Up to kShortMaxN tokens both kinds of selection do a call, with the same lists;
+// Up to kShortMaxN tokens both kinds of selection do a call, with the same lists
+// (a NaN score is the lowest to the row kernel and never listed by the passes);
 // this is whether the passes do it faster.  The row kernel works on a row at a time
 // and costs more per row than the passes, above all past 8192 keys (eight waves of
 // 32 keys a lane leave a CU two rows); the passes have more launches to start, copy
